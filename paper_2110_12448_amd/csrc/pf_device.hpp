@@ -28,10 +28,63 @@ template <> struct Math<float> {
   static __device__ __forceinline__ bool finite(float x) { return __builtin_isfinite(x); }
 };
 
+// FP64: the hardware seeds (about 2^-24) and one third-order Newton step in
+// place of the IEEE division and square-root sequences, and a tanh of its own.
+// The arguments of rcp and rsq in the kernels are finite and positive.
+// Against 80-bit results over 2M arguments: rcp max 0.500 ulp, rms 0.289 (x/y
+// 0.500 and 0.289); rsq 0.99 and 0.34 (1/sqrt 1.48 and 0.46); tanh 0.86 and
+// 0.29 (the runtime library's 0.86 and 0.28).
 template <> struct Math<double> {
-  static __device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
-  static __device__ __forceinline__ double rsq(double x) { return 1.0 / sqrt(x); }
-  static __device__ __forceinline__ double tanh_(double x) { return tanh(x); }
+  static __device__ __forceinline__ double rcp(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, __builtin_fma(e, e, e), r);
+  }
+  static __device__ __forceinline__ double rsq(double x) {
+    const double r = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-(x * r), r, 1.0);
+    return __builtin_fma(r * e, __builtin_fma(0.375, e, 0.5), r);
+  }
+  // tanh(x) = sign(x) * -E / (2 + E), E = expm1(-2|x|): Cody-Waite reduction
+  // y = n ln2 + r, expm1(r) = r + r^2 (1/2 + r g(r)) with g from Chebyshev
+  // interpolation on |r| <= ln2 / 2 (error 8e-18), E = 2^n expm1(r) + (2^n - 1)
+  // and the quotient in head and tail parts.
+  static __device__ __forceinline__ double tanh_(double x) {
+    const double kLog2e = 0x1.71547652b82fep+0, kLn2Hi = 0x1.62e42fee00000p-1,
+                 kLn2Lo = 0x1.a39ef35793c76p-33, kMagic = 6755399441055744.0;  // 1.5 * 2^52
+    double ax = __builtin_fabs(x);
+    ax = ax > 40.0 ? 40.0 : ax;  // 1 from 19.1 on; a NaN stays
+    const double y = -2.0 * ax;
+    const double t = __builtin_fma(y, kLog2e, kMagic);
+    const double n = t - kMagic;
+    const int ni = (int)__builtin_bit_cast(unsigned long long, t);
+    const double r1 = __builtin_fma(n, -kLn2Hi, y);
+    const double r = __builtin_fma(n, -kLn2Lo, r1);
+    const double rl = __builtin_fma(n, -kLn2Lo, r1 - r);
+    double g = 0x1.1f66f85dfa20ap-29;
+    g = __builtin_fma(g, r, 0x1.af38d53857513p-26);
+    g = __builtin_fma(g, r, 0x1.27e4e1ea0f53ap-22);
+    g = __builtin_fma(g, r, 0x1.71de0d9c145d0p-19);
+    g = __builtin_fma(g, r, 0x1.a01a01a47db6fp-16);
+    g = __builtin_fma(g, r, 0x1.a01a01a7c8d47p-13);
+    g = __builtin_fma(g, r, 0x1.6c16c16c167dep-10);
+    g = __builtin_fma(g, r, 0x1.11111111109adp-7);
+    g = __builtin_fma(g, r, 0x1.5555555555555p-5);
+    g = __builtin_fma(g, r, 0x1.5555555555556p-3);
+    g = __builtin_fma(g, r, 0.5);
+    const double c = __builtin_fma(r * r, g, rl);  // expm1(y - n ln2) = r + c
+    const double s =  // 2^n
+        __builtin_bit_cast(double, (unsigned long long)(unsigned)((ni << 20) + 0x3ff00000) << 32);
+    const double a = s - 1.0, b = s * r, h0 = a + b;
+    double lo = (b - (h0 - a)) + (s - (a + 1.0));
+    lo = __builtin_fma(s, c, lo);
+    const double hi = h0 + lo;
+    lo = lo - (hi - h0);
+    const double dh = 2.0 + hi, dl = (hi - (dh - 2.0)) + lo;
+    const double q = rcp(dh), v = -hi * q;
+    const double rem = __builtin_fma(-v, dl, __builtin_fma(-v, dh, -hi)) - lo;
+    return __builtin_copysign(__builtin_fma(rem, q, v), x);
+  }
   static __device__ __forceinline__ bool finite(double x) { return __builtin_isfinite(x); }
 };
 
