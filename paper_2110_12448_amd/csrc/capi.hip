@@ -257,7 +257,7 @@ namespace {
 // asks for waves per SIMD).
 int rows2d(const pf_solver *s) {
   if (s->seg > 0) return s->seg;
-  const Geom2D g = geom2d(s->p.nx, s->p.ny, s->seg, s->ncu);
+  const Geom2D g = geom2d(s->p.nx, s->p.ny, s->seg, s->ncu, false);
   return g.segbase + (g.segrem ? 1 : 0);
 }
 
@@ -365,12 +365,12 @@ int8_t *grain_buf(pf_solver *s, int k) {
 
 // Argument block of the 2D step of solver s (pointers set per launch).
 template <typename T>
-Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, int min_seg = 1, int seg_fixed = 0) {
+Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, bool share, int min_seg = 1, int seg_fixed = 0) {
   const pf_params &p = s->p;
   memset(&a, 0, sizeof(a));
-  Geom2D g = seg_fixed > 0   ? geom2d(p.nx, p.ny, seg_fixed)
-             : min_seg <= 1 ? geom2d(p.nx, p.ny, s->seg, s->ncu)
-                            : geom2d(p.nx, p.ny, std::max(rows2d(s), min_seg));
+  Geom2D g = seg_fixed > 0   ? geom2d(p.nx, p.ny, seg_fixed, 0, share)
+             : min_seg <= 1 ? geom2d(p.nx, p.ny, s->seg, s->ncu, share)
+                            : geom2d(p.nx, p.ny, std::max(rows2d(s), min_seg), 0, share);
   a.grain = p.n_grains > 1 ? grain_buf(s, s->cur) : nullptr;
   a.grain_out = p.dynamic_grains ? grain_buf(s, 1 - s->cur) : nullptr;
   a.rot = field<T>(s, s->L.rot);
@@ -378,6 +378,7 @@ Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, int min_seg = 1, int seg_fixed = 0
   a.nx = p.nx; a.ny = p.ny; a.bcx = p.bc[0]; a.bcy = p.bc[1];
   a.wout = g.wout; a.nstrips = g.nstrips; a.nsegs = g.nsegs;
   a.segbase = g.segbase; a.segrem = g.segrem;
+  a.shared = g.shared;
   a.c = coef_of<T>(s);
   a.hd = p.h; a.y0 = p.y0; a.Vp = p.Vp; a.dtd = s->dt;
   a.frame = p.frame; a.shift_row = p.shift_row;
@@ -394,7 +395,7 @@ int step_impl(pf_solver *s, long long nsteps, bool diffusion_only = false) {
   auto frec = [&](int i) { return reinterpret_cast<FrameState *>(s->ws + s->L.frame[i % 3]); };
   if (p.dim == 2) {
     Step2DArgs<T> a;
-    Geom2D g = fill2d<T>(s, a);
+    Geom2D g = fill2d<T>(s, a, !diffusion_only);
     (void)c;
     const bool two = p.divergence == PF_DIV_TWO_POINT;
     const int at = diffusion_only ? kAtDiffusionOnly
@@ -537,7 +538,7 @@ int batch_build(pf_batch *b) {
     pf_solver *s = b->s[i];
     BatchSolve2D<T> &e = tab[i];
     memset(&e, 0, sizeof(e));
-    Geom2D g = fill2d<T>(s, e.a, kMinSegBatch2D, b->seg_fixed);
+    Geom2D g = fill2d<T>(s, e.a, true, kMinSegBatch2D, b->seg_fixed);
     for (int k = 0; k < 2; ++k) {
       e.psi[k] = field<T>(s, s->L.psi[k]);
       e.U[k] = field<T>(s, s->L.U[k]);
@@ -709,9 +710,9 @@ int autotune_impl(pf_solver *s, int steps) {
   if (s->p.dim == 2) {
     // waves per SIMD; counts that give the same segments as one already
     // listed are skipped
-    std::vector<int> nsegs = {geom2d(s->p.nx, s->p.ny, s->seg, s->ncu).nsegs};
+    std::vector<int> nsegs = {geom2d(s->p.nx, s->p.ny, s->seg, s->ncu, true).nsegs};
     for (int k : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
-      const int n = geom2d(s->p.nx, s->p.ny, -k, s->ncu).nsegs;
+      const int n = geom2d(s->p.nx, s->p.ny, -k, s->ncu, true).nsegs;
       if (std::find(nsegs.begin(), nsegs.end(), n) != nsegs.end()) continue;
       nsegs.push_back(n);
       add(-k, s->ztile);

@@ -79,6 +79,7 @@ struct Step2DArgs {
   T r00, r01, r10, r11;  // single grain
   int nx, ny, bcx, bcy;
   int wout, nstrips, nsegs, segbase, segrem;
+  int shared;            // waves of a workgroup share a strip and their junctions
   Coef<T> c;
   double hd, y0, Vp, dtd;
   long long step;
@@ -138,9 +139,9 @@ struct ReduceArgs {
 // many as give k waves per SIMD over ncu compute units (at most ny); the rows
 // are split evenly (segbase rows each, one more for the first segrem).
 struct Geom2D {
-  int wout, nstrips, nsegs, seg, segbase, segrem, blocks;
+  int wout, nstrips, nsegs, seg, segbase, segrem, blocks, shared;
 };
-Geom2D geom2d(int nx, int ny, int seg, int ncu = 0);
+Geom2D geom2d(int nx, int ny, int seg, int ncu, bool share);
 
 // Launch geometry of the 3D step: nstrips strips of wout output columns
 // (wide tiles, one z row per wave) and, when at most 17 of nx mod 60 columns

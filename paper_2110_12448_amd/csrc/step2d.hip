@@ -124,6 +124,14 @@ template <typename T, bool kMulti>
 constexpr int kMinWavesBatch2D = sizeof(T) == 4 ? 4 : kMinWaves2D<T, kMulti, kAtApproxShells>;
 
 // One logical workgroup `lb` (4 waves) of the step of one solve `a`.
+//
+// Shared segments (a.shared): the 4 waves of a workgroup hold consecutive
+// segments of one strip, and each wave but the top one takes the U rows y0 + 1
+// .. ye (the bottom one y0 too) with alpha_A of rows ye and ye + 1 from the
+// wave above, which leaves them in LDS when it has started; so the psi rate of
+// a junction row is computed once, and a wave above the bottom one starts
+// without the row below its segment.  Otherwise the 4 waves are independent
+// (neighbouring strips), each with its own start and end.
 template <typename T, bool kFrozen, bool kReduce, bool kMulti, int kAT, bool kRowTail = true>
 __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb) {
   constexpr bool kTwoPoint = kAT == kAtFullTwoPoint || kAT == kAtApproxTwoPoint;
@@ -132,13 +140,20 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
   const Coef<T> &c = a.c;
   const int lane = threadIdx.x & 63;
   // wave-uniform: keeps strip, segment and row counters in scalar registers
-  const int wave = lb * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wave = lb * 4 + wv;
   const int nx = a.nx, ny = a.ny;
 
   bool over_any = false;
 
+  __shared__ T xA[4][2][64];  // alpha_A of the first two rows of each wave (shared segments)
+  const bool shared = !kDiff && a.shared;
+  const bool first = !shared || wv == 0, last = !shared || wv == 3;
+
   if (wave < a.nstrips * a.nsegs) {
-    const int strip = wave % a.nstrips, segi = wave / a.nstrips;
+    // shared: nsegs is a multiple of 4, so every wave of the workgroup is here
+    const int strip = shared ? lb % a.nstrips : wave % a.nstrips;
+    const int segi = shared ? 4 * (lb / a.nstrips) + wv : wave / a.nstrips;
     const int x = strip * a.wout - 2 + lane;
     const int gx = ghost(x, nx, a.bcx);
     const bool out_lane = lane >= 2 && lane < 2 + a.wout && x < nx;
@@ -194,8 +209,12 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     // rows r, r+1, r+2 in flight (loads issued two iterations ahead)
     T lp0, lu0, lp1, lu1, lp2, lu2;
     int lg0 = 0, lg1 = 0, lg2 = 0;
+    const int rs = first ? y0 - 2 : y0 - 1;  // first row read
+    // last row read: one past the segment, or two for App. B's gradients on
+    // the U row ye
+    const int rl = ye + (kAT == kAtFullShells && !last ? 2 : 1);
     {
-      size_t o0 = prow(y0 - 2), o1 = prow(y0 - 1), o2 = prow(y0);
+      size_t o0 = prow(rs), o1 = prow(rs + 1), o2 = prow(rs + 2);
       lp0 = a.psi_in[o0]; lu0 = a.U_in[o0];
       lp1 = a.psi_in[o1]; lu1 = a.U_in[o1];
       lp2 = a.psi_in[o2]; lu2 = a.U_in[o2];
@@ -205,7 +224,10 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     // One row of the pipeline.  P is the pipeline phase: 0 loads only (row
     // y0-2), 1 adds the y face flux, 2 the psi rate of row y0-1, 3 the first
     // stored psi row and the divergence carries of the pair (y0-1, y0), 4 is
-    // the steady state with every stage active.
+    // the steady state with every stage active.  Waves that start on a shared
+    // junction run 0 and 1 one row later, then 7 (psi rate of row y0, stored)
+    // and 3 on the pair (y0, y0+1); waves that end on one run 8 and 9, the
+    // divergences of rows ye-1 and ye with alpha_A taken from xA.
     // moving-frame decision: an interface cell of row m whose
     // phi = 0 crossing lies at or above the shift row.  Rows at or above it
     // qualify outright and rows below the one under it cannot (the crossing
@@ -233,17 +255,17 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       pN = lp0; uN = lu0; gN = lg0;
       lp0 = lp1; lu0 = lu1; lg0 = lg1;
       lp1 = lp2; lu1 = lu2; lg1 = lg2;
-      if (P >= 5 || r + 3 <= ye + 1) {
-        // steady state: the last rows reload row ye + 1 (never consumed)
-        // instead of branching around the load
-        size_t on = P >= 5 ? prow_top(min(r + 3, ye + 1)) : prow(r + 3);
+      if (P < 8 && (P >= 5 || r + 3 <= rl)) {
+        // steady state: the last rows reload row rl (never consumed) instead
+        // of branching around the load
+        size_t on = P >= 5 ? prow_top(min(r + 3, rl)) : prow(r + 3);
         lp2 = a.psi_in[on];
         lu2 = a.U_in[on];
         if (kMulti) lg2 = a.grain[on];
       }
       pNW = from_left(pN);
       pNE = from_right(pN);
-      fN = M::tanh_(pN * isq2);
+      if (P != 9) fN = M::tanh_(pN * isq2);  // phase 9's row r is past every use of phi
       if constexpr (P == 0) return;
       if constexpr (kAT == kAtFullShells && P >= 2) {
         pCE2 = from_right(pCE);
@@ -253,7 +275,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // y face between rows r-1 and r, grain of the lower cell; face
       // fluxes are h J (gradients passed as h g)
       T FyN = T(0);
-      if constexpr (!kDiff)
+      if constexpr (!kDiff && P < 8)
         FyN = aniso_flux<T, 1>(T(0.25) * (pNE + pCE - pNW - pCW), pN - pC, c.at_eps, rot_of(gC),
                                c);
       // dynamic grains: the grain of row m at the next level (a liquid cell,
@@ -283,7 +305,9 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
           }
         }
       };
-      if constexpr (P >= 2 && kDiff) {
+      if constexpr (P >= 8) {
+        aAC = xA[(wv + 1) & 3][P - 8][lane];  // row m = r - 1 of the wave above
+      } else if constexpr (P >= 2 && kDiff) {
         // psi is held: copy row m and take the frame decision on it
         const int m = r - 1;
         grain_next(m);
@@ -319,7 +343,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         T rhs = ac2 * (L - sq2 * ph * G) + Nn + sq2 * (ph - c.lambda * omp * F2);
         T rate = rhs * M::rcp(F1 * ac2);
         T aA = (T(1) + c.omk * uC) * omp * rate * T(0.5);
-        if (P == 6 || (P < 5 && a.bcx == PF_BC_NOFLUX)) {  // mirrored columns copy their image
+        if (P == 6 || ((P < 5 || P == 7) && a.bcx == PF_BC_NOFLUX)) {  // mirrored columns copy their image
           T fr = from_right(aA), fl = from_left(aA);
           aA = (x == -1) ? fr : ((x == nx) ? fl : aA);
         }
@@ -342,7 +366,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // alpha_D = D~ (1 - phi) and lambda = 1, or h for the full current (whose
       // links carry h / |h grad psi|): one set of sums, lane moves and carries.
       constexpr bool kFullAT = kAT == kAtFullShells || kAT == kAtFullTwoPoint;
-      if constexpr (P >= 3 && kTwoPoint) {
+      if constexpr (P >= 3 && P != 7 && kTwoPoint) {
         // <10> faces: east face of row q and north face (q+1/2)
         const int q = r - 2;
         T aq = c.D - c.D * fS, aq1 = c.D - c.D * fC;
@@ -373,7 +397,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
           store_row(a.U_out + (size_t)q * (size_t)nx, nx, x, out_lane, uS + c.dt * rU);
         }
         cN = fN;
-      } else if constexpr (P >= 3) {
+      } else if constexpr (P >= 3 && P != 7) {
         // shells on the row pair (q, q+1) = (S, C): field D alpha = D~(1 - phi),
         // beta = U; field A alpha = alpha_A, beta = psi
         const int q = r - 2;
@@ -469,10 +493,24 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     using I4 = std::integral_constant<int, 4>;
     using I5 = std::integral_constant<int, 5>;  // phase 4 on rows 1..ny-1
     using I6 = std::integral_constant<int, 6>;  // phase 5, mirrored x columns
-    iter(I0{}, y0 - 2);
-    iter(I1{}, y0 - 1);
-    iter(I2{}, y0);
-    iter(I3{}, y0 + 1);
+    using I7 = std::integral_constant<int, 7>;
+    using I8 = std::integral_constant<int, 8>;
+    using I9 = std::integral_constant<int, 9>;
+    iter(I0{}, rs);
+    iter(I1{}, rs + 1);
+    if (first) {
+      iter(I2{}, y0);
+    } else {
+      iter(I7{}, y0 + 1);
+      xA[wv][0][lane] = aAC;
+    }
+    iter(I3{}, rs + 3);
+    if constexpr (!kDiff) {
+      if (shared) {
+        xA[wv][1][lane] = aAC;
+        __syncthreads();
+      }
+    }
     // steady state unrolled by 6, a multiple of every register-rotation
     // period (3 for the row window, the grains and the loads in flight, 2 for
     // alpha_A, 1 for the carries), so the rotation costs no register moves.
@@ -484,7 +522,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     // Without kRowTail (batched launches: long segments, and waves of many
     // solves at different points of the code) they take phase 4, which keeps
     // the code smaller.
-    int r = y0 + 2;
+    int r = rs + 4;
     if (a.bcx == PF_BC_NOFLUX) {  // phase 6: phase 5 with mirrored columns
       for (; r + 5 <= ye; r += 6) {
         iter(I6{}, r);
@@ -508,7 +546,14 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       if constexpr (kRowTail)
         for (; r <= ye; ++r) iter(I5{}, r);
     }
-    for (; r <= ye + 1; ++r) iter(I4{}, r);
+    if (last) {
+      for (; r <= ye + 1; ++r) iter(I4{}, r);
+    } else if constexpr (!kDiff) {
+      if constexpr (!kRowTail)
+        for (; r <= ye; ++r) iter(I4{}, r);
+      iter(I8{}, ye + 1);
+      iter(I9{}, ye + 2);
+    }
     if (kReduce) {
       // the row under the shift row: its crossing height in FP64, on the phi
       // the pipeline computed from the same loads
@@ -583,7 +628,9 @@ __global__ void batch2d_advance(BatchSolve2D<T> *table, int n, int steps, int fr
 
 }  // namespace
 
-Geom2D geom2d(int nx, int ny, int seg, int ncu) {
+constexpr int kMinRowsShared2D = 3;
+
+Geom2D geom2d(int nx, int ny, int seg, int ncu, bool share) {
   Geom2D g;
   g.nstrips = (nx + 59) / 60;
   g.wout = (nx + g.nstrips - 1) / g.nstrips;
@@ -595,6 +642,11 @@ Geom2D geom2d(int nx, int ny, int seg, int ncu) {
     const long long want = (long long)(-g.seg) * 4 * (ncu > 0 ? ncu : 1) / g.nstrips;
     g.nsegs = (int)std::max(1LL, std::min((long long)ny, want));
   }
+  // shared segments need a multiple of 4 of them (rounded down for a number
+  // of waves, up for a number of rows) and rows enough
+  const int n4 = g.seg > 0 ? (g.nsegs + 3) / 4 * 4 : g.nsegs / 4 * 4;
+  g.shared = share && n4 > 0 && ny / n4 >= kMinRowsShared2D ? 1 : 0;
+  if (g.shared) g.nsegs = n4;
   g.segbase = ny / g.nsegs;
   g.segrem = ny % g.nsegs;
   int waves = g.nstrips * g.nsegs;
