@@ -293,10 +293,20 @@ Coef<T> coef_of(const pf_solver *s) {
     c.cG1 = (T)(s->w[0] / (4.0 * h2));
     c.cG2 = (T)(s->w[1] / (8.0 * h2));
     c.cG3 = (T)0;
+    // the psi equation times h^2 (its eps4 remainder holds -s10 / h^2)
+    c.rA1 = (T)(s->w[0] - 1.0);
+    c.rA2 = (T)(s->w[1] / 2.0);
+    c.rB1 = (T)(-sqrt(2.0) * s->w[0] / 4.0);
+    c.rB2 = (T)(-sqrt(2.0) * s->w[1] / 8.0);
+    c.rK = (T)(sqrt(2.0) * h2);
+    c.h2 = (T)h2;
+    c.omkh2 = (T)((1.0 - p.k) * h2);
+    c.hT = (T)(p.lT > 0.0 ? h / p.lT : 0.0);
     // D_{1,0}: fluxes carry the 4-point alpha sum, /(4h^2); D_{0,1}: plaquette
-    // means times dbeta, /(2h^2) (Eqs. flux_10, flux_11)
-    c.cD1 = (T)(s->w[0] / (4.0 * h2));
-    c.cD2 = (T)(s->w[1] / (2.0 * h2));
+    // means times dbeta, /(2h^2) (Eqs. flux_10, flux_11); the kernel's link
+    // alphas carry another factor 4
+    c.cD1 = (T)(s->w[0] / (16.0 * h2));
+    c.cD2 = (T)(s->w[1] / (8.0 * h2));
     c.cD3 = (T)0;
     // two-point faces carry (alpha_0 + alpha_e) dbeta: /(2h^2); links of the
     // full current carry h / |h grad psi| and enter with a factor h
@@ -304,6 +314,7 @@ Coef<T> coef_of(const pf_solver *s) {
     c.at_eps = (T)(1e-12 * h2);
     c.ac_eps = (T)(4e-12 * h2);
     c.an1 = (T)(1.0 + p.eps4);
+    c.an2 = (T)(2.0 * p.eps4);
     c.an8 = (T)(8.0 * p.eps4);
   } else {
     // L_{1,0,0} = s/h^2, L_{0,1,0} = s/(4h^2), L_{0,0,1} = s/(4h^2)
@@ -330,6 +341,12 @@ Coef<T> coef_of(const pf_solver *s) {
   return c;
 }
 
+// cos and sin of twice the angle of a rotation about z (row-major 3 x 3)
+void double_angle(const double *R, double *c2, double *s2) {
+  *c2 = R[0] * R[4] + R[1] * R[3];
+  *s2 = R[3] * R[0] - R[1] * R[4];
+}
+
 template <typename T>
 int upload(pf_solver *s, const pf_init *init) {
   const size_t n = s->n;
@@ -338,16 +355,16 @@ int upload(pf_solver *s, const pf_init *init) {
   PF_HIP(hipMemcpy(field<T>(s, s->L.psi[0]), tmp.data(), n * sizeof(T), hipMemcpyHostToDevice));
   for (size_t i = 0; i < n; ++i) tmp[i] = (T)init->U[i];
   PF_HIP(hipMemcpy(field<T>(s, s->L.U[0]), tmp.data(), n * sizeof(T), hipMemcpyHostToDevice));
-  // rotation table: 2D (r00, r01, r10, r11) per grain, 3D all 9
+  // rotation table: 2D (cos, sin of twice the angle) per grain, 3D all 9
   const int ng = s->p.n_grains;
   std::vector<T> rt((size_t)ng * 9, (T)0);
   for (int g = 0; g < ng; ++g) {
     const double *R = s->rot.data() + 9 * g;
     if (s->p.dim == 2) {
-      rt[4 * g + 0] = (T)R[0];
-      rt[4 * g + 1] = (T)R[1];
-      rt[4 * g + 2] = (T)R[3];
-      rt[4 * g + 3] = (T)R[4];
+      double c2, s2;
+      double_angle(R, &c2, &s2);
+      rt[2 * g + 0] = (T)c2;
+      rt[2 * g + 1] = (T)s2;
     } else {
       for (int i = 0; i < 9; ++i) rt[9 * g + i] = (T)R[i];
     }
@@ -374,13 +391,16 @@ Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, bool share, int min_seg = 1, int s
   a.grain = p.n_grains > 1 ? grain_buf(s, s->cur) : nullptr;
   a.grain_out = p.dynamic_grains ? grain_buf(s, 1 - s->cur) : nullptr;
   a.rot = field<T>(s, s->L.rot);
-  a.r00 = (T)s->rot[0]; a.r01 = (T)s->rot[1]; a.r10 = (T)s->rot[3]; a.r11 = (T)s->rot[4];
+  double c2, s2;
+  double_angle(s->rot.data(), &c2, &s2);
+  a.c2 = (T)c2; a.s2 = (T)s2;
   a.nx = p.nx; a.ny = p.ny; a.bcx = p.bc[0]; a.bcy = p.bc[1];
   a.wout = g.wout; a.nstrips = g.nstrips; a.nsegs = g.nsegs;
   a.segbase = g.segbase; a.segrem = g.segrem;
   a.shared = g.shared;
   a.c = coef_of<T>(s);
   a.hd = p.h; a.y0 = p.y0; a.Vp = p.Vp; a.dtd = s->dt;
+  a.inv_lTd = p.lT > 0.0 ? 1.0 / p.lT : 0.0;
   a.frame = p.frame; a.shift_row = p.shift_row;
   return g;
 }

@@ -17,13 +17,12 @@ template <typename T> struct Math;
 template <> struct Math<float> {
   static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
   static __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
-  // tanh(x) = sign(x) (1 - e) / (1 + e), e = exp(-2|x|), with the hardware
-  // base-2 exponential; absolute error a few ulp of 1.
-  static __device__ __forceinline__ float tanh_(float x) {
-    const float m2log2e = -2.8853900817779268f;  // -2 / ln 2
-    float e = __builtin_amdgcn_exp2f(m2log2e * __builtin_fabsf(x));
-    float t = (1.0f - e) * __builtin_amdgcn_rcpf(1.0f + e);
-    return __builtin_copysignf(t, x);
+  // phi = tanh(psi / sqrt2) = sign(psi) (1 - e) / (1 + e), e = exp(-sqrt2
+  // |psi|), with the hardware base-2 exponential; absolute error a few ulp of 1.
+  static __device__ __forceinline__ float phi(float psi) {
+    const float c = -2.0402789f;  // -sqrt2 / ln 2
+    const float e = __builtin_amdgcn_exp2f(c * __builtin_fabsf(psi));
+    return __builtin_copysignf((1.0f - e) * __builtin_amdgcn_rcpf(1.0f + e), psi);
   }
   static __device__ __forceinline__ bool finite(float x) { return __builtin_isfinite(x); }
 };
@@ -84,6 +83,9 @@ template <> struct Math<double> {
     const double q = rcp(dh), v = -hi * q;
     const double rem = __builtin_fma(-v, dl, __builtin_fma(-v, dh, -hi)) - lo;
     return __builtin_copysign(__builtin_fma(rem, q, v), x);
+  }
+  static __device__ __forceinline__ double phi(double psi) {
+    return tanh_(psi * 0.70710678118654752);
   }
   static __device__ __forceinline__ bool finite(double x) { return __builtin_isfinite(x); }
 };

@@ -61,7 +61,11 @@ struct Coef {
   T cT;             // two-point <10> faces: 1/(2h^2) (2D)
   T at_eps;         // 1e-12 h^2: the |g|^2 <= 1e-12 guard for h g (face gradients, 2D)
   T ac_eps;         // 4e-12 h^2: the same guard for 2h g (centre differences)
-  T an1, an8;       // 1 + eps4, 8 eps4 (2D a_s = 1 + eps4 - 8 eps4 u^2 v^2)
+  T an1, an2, an8;  // 1 + eps4, 2 eps4, 8 eps4 (2D a_s = 1 + eps4 cos 4t)
+  T rA1, rA2;       // h^2 times the shell weights of L, the standard Laplacian off the first (2D)
+  T rB1, rB2;       // -sqrt2 h^2 times the shell weights of G over their prefactors (2D)
+  T rK, h2, omkh2;  // sqrt2 h^2, h^2, (1 - k) h^2 (2D)
+  T hT;             // h / lT, 0 when isothermal (2D)
   T k1a, k1b;       // cD1/4, cD1/16: <100> link alpha weights times the shell coefficient (3D)
   T k2a, k2b;       // 3 cD2/16, cD2/32: the same for <110> links (3D)
   T k3;             // cD3/8: <111> links, mean of the 8 cube corners (3D)
@@ -75,13 +79,13 @@ struct Step2DArgs {
   T *psi_out, *U_out;
   const int8_t *grain;   // multi-grain only
   int8_t *grain_out;     // dynamic grains only: grain map of the next level
-  const T *rot;          // multi-grain only: 4 per grain (r00, r01, r10, r11)
-  T r00, r01, r10, r11;  // single grain
+  const T *rot;          // multi-grain only: (c2, s2) per grain
+  T c2, s2;              // single grain: cos and sin of twice its angle
   int nx, ny, bcx, bcy;
   int wout, nstrips, nsegs, segbase, segrem;
   int shared;            // waves of a workgroup share a strip and their junctions
   Coef<T> c;
-  double hd, y0, Vp, dtd;
+  double hd, y0, Vp, dtd, inv_lTd;
   long long step;
   int frame, shift_row;
   const FrameState *frame_in;

@@ -50,7 +50,6 @@ __global__ __launch_bounds__(64 * kReduceWaves) void reduce_kernel(ReduceArgs<T>
   const int rows = a.rows;
   const int nsegs = (ny + rows - 1) / rows;
   const long long items = (long long)nstrips * nsegs * nz;
-  const T isq2 = T(0.70710678118654752);
   const size_t plane = (size_t)nx * (size_t)ny;
   TipAcc acc;
   tip_init(acc);
@@ -87,14 +86,14 @@ __global__ __launch_bounds__(64 * kReduceWaves) void reduce_kernel(ReduceArgs<T>
         uv[k] = a.U[base + srow(j)];
         pv[k] = a.psi[base + srow(min(j + 1, ny - 1))];
       }
-      if (j0 == y0) f = M::tanh_(p * isq2);
+      if (j0 == y0) f = M::phi(p);
 #pragma unroll
       for (int k = 0; k < kChunk; ++k) {
         const int j = j0 + k;
         if (j < ye) {
           const bool up = j + 1 < ny;
           const T pn = pv[k];
-          const T fn = M::tanh_(pn * isq2);
+          const T fn = M::phi(pn);
           sf += (double)f;
           bad += (M::finite(p) && M::finite(uv[k])) ? 0u : 1u;
           const bool cr = up && f >= T(0) && fn < T(0);

@@ -52,9 +52,10 @@ namespace pf {
 
 namespace {
 
+// Rotation of the crystal by alpha0: cos and sin of 2 alpha0.
 template <typename T>
 struct Rot2 {
-  T r00, r01, r10, r11;  // crystal -> lab
+  T c2, s2;
 };
 
 // Both functions take the gradient in any positive multiple of its true
@@ -63,35 +64,36 @@ struct Rot2 {
 // for g~ (1e-12 s^2): at or below it a_s = 1 and J = g~.
 //
 // In 2D the cubic form of Eq. anis_function, a_s = 1 - 3 eps4 + 4 eps4
-// (u^4 + v^4) with (u, v) = R^T g/|g|, equals 1 + eps4 - 8 eps4 u^2 v^2
-// (= 1 + eps4 cos 4(theta - alpha0)).
+// (u^4 + v^4) with (u, v) = R^T g/|g|, equals 1 + eps4 cos 4t, t the angle of
+// g in the crystal frame.  sin 2t = w/|g|^2 and cos 2t = v/|g|^2 with
+// w = C 2 gx gy - S (gx^2 - gy^2), v = C (gx^2 - gy^2) + S 2 gx gy: two
+// constants per crystal, which fit vector registers.  On gfx950 an FP32
+// instruction with an SGPR operand issues at half the rate of one without
+// (4.9 against 2.7 cycles a wave measured at 4 waves per SIMD), as do lane
+// moves, compares and selects.
 template <typename T>
 __device__ __forceinline__ T aniso_a(T gx, T gy, T g2eps, const Rot2<T> &R, const Coef<T> &c) {
-  T g2 = gx * gx + gy * gy;
-  T r2 = Math<T>::rcp(g2 > g2eps ? g2 : g2eps);
-  T cx = R.r00 * gx + R.r10 * gy;
-  T cy = R.r01 * gx + R.r11 * gy;
-  T w = cx * cy * r2;
-  T a = c.an1 - c.an8 * w * w;
+  const T g2 = gx * gx + gy * gy, d = gx * gx - gy * gy, p2 = (gx + gx) * gy;
+  const T wn = (R.c2 * p2 - R.s2 * d) * Math<T>::rcp(g2);
+  const T a = c.an1 - (c.an2 * wn) * wn;  // 1 + eps4 - 2 eps4 sin^2 2t
   return g2 > g2eps ? a : T(1);
 }
 
 // Component `comp` (0: x, 1: y) of the anisotropic flux
-// J = a^2 g + |g|^2 a da/dg.  In 2D the second term is a (da/dtheta) g_perp,
-// g_perp = (-gy, gx), with da/dtheta = -16 eps4 u v (u^2 - v^2).
+// J = a^2 g + |g|^2 a da/dg.  In 2D the second term is a (da/dt) g_perp,
+// g_perp = (-gy, gx), with da/dt = -8 eps4 sin 2t cos 2t.  Below the guard
+// the normalisation 1/|g|^2 is taken as 0, which leaves a = 1 and J = g.
 template <typename T, int comp>
 __device__ __forceinline__ T aniso_flux(T gx, T gy, T g2eps, const Rot2<T> &R,
                                         const Coef<T> &c) {
-  T g2 = gx * gx + gy * gy;
-  T r2 = Math<T>::rcp(g2 > g2eps ? g2 : g2eps);
-  T cx = R.r00 * gx + R.r10 * gy;
-  T cy = R.r01 * gx + R.r11 * gy;
-  T w = cx * cy * r2;
-  T a = c.an1 - c.an8 * w * w;
-  T ath = c.an16 * w * ((cx * cx - cy * cy) * r2);  // -da/dtheta
-  T j = comp == 0 ? a * (a * gx + ath * gy) : a * (a * gy - ath * gx);
-  T plain = comp == 0 ? gx : gy;
-  return g2 > g2eps ? j : plain;
+  const T g2 = gx * gx + gy * gy, d = gx * gx - gy * gy, p2 = (gx + gx) * gy;
+  const T rg = Math<T>::rcp(g2);
+  const T r2 = g2 > g2eps ? rg : T(0);
+  const T wn = (R.c2 * p2 - R.s2 * d) * r2;
+  const T vn = (R.c2 * d + R.s2 * p2) * r2;
+  const T a = T(1) + c.eps4 * (vn * vn - wn * wn);
+  const T ath = (c.an8 * wn) * vn;  // -da/dt
+  return comp == 0 ? a * (a * gx + ath * gy) : a * (a * gy - ath * gx);
 }
 
 // Logical blocks -> hardware blocks so that each of the 8 XCDs (which take
@@ -155,19 +157,20 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     const int strip = shared ? lb % a.nstrips : wave % a.nstrips;
     const int segi = shared ? 4 * (lb / a.nstrips) + wv : wave / a.nstrips;
     const int x = strip * a.wout - 2 + lane;
-    const int gx = ghost(x, nx, a.bcx);
+    // x <= nx + 60: within one period unless the lattice is narrow
+    const int gx = nx >= 62 ? ghost_near(x, nx, a.bcx) : ghost(x, nx, a.bcx);
     const bool out_lane = lane >= 2 && lane < 2 + a.wout && x < nx;
     // rows split evenly: the first segrem segments take one row more
     const int y0 = segi * a.segbase + min(segi, a.segrem);
     const int ye = y0 + a.segbase + (segi < a.segrem ? 1 : 0);
     const int pend = a.frame ? a.frame_in->pending : 0;
     const long long shift = a.frame ? a.frame_in->base + pend : 0;
-    T off = T(0);
-    if (kFrozen) off = (T)((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd));
+    T offT = T(0);  // zeta / lT of row 0
+    if (kFrozen)
+      offT = (T)(((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd)) * a.inv_lTd);
     const double ythr = (double)a.shift_row * a.hd;
     bool over = false;  // this lane saw a crossing at or above the shift row
     const T sq2 = T(1.4142135623730951);
-    const T isq2 = T(0.70710678118654752);
 
     auto prow = [&](int r) -> size_t {
       int j = ghost_near(r, ny, a.bcy);
@@ -183,12 +186,17 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       const int j = r - top_per * min(over, 1) - top_mir * max(2 * over - 1, 0);
       return (size_t)min(j + pend, ny - 1) * (size_t)nx + (size_t)gx;
     };
+    // a single grain's rotation and the coefficients read most per row live
+    // in vector registers (see aniso_a)
+    Rot2<T> R0{a.c2, a.s2};
+    if constexpr (sizeof(T) == 4 && !kMulti && !kDiff)
+      asm volatile("" : "+v"(R0.c2), "+v"(R0.s2));
     auto rot_of = [&](int g) -> Rot2<T> {
       if (kMulti) {
-        const T *q = a.rot + 4 * g;
-        return Rot2<T>{q[0], q[1], q[2], q[3]};
+        const T *q = a.rot + 2 * g;
+        return Rot2<T>{q[0], q[1]};
       }
-      return Rot2<T>{a.r00, a.r01, a.r10, a.r11};
+      return R0;
     };
 
     // register window: S = row r-2, C = row r-1, N = row r (newest)
@@ -198,6 +206,9 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     T aAS = 0, aAC = 0;
     int gS = 0, gC = 0, gN = 0;
     T FyS = 0;  // y face flux below row r-1
+    // per row: x central difference (row C) and sum of the two x neighbour
+    // differences (rows C, S); pN - pC of the row before
+    T exC = 0, exN = 0, sxS = 0, sxC = 0, sxN = 0, dNp = 0, dN = 0;
     // carries of the divergence for the row pair below (q-1, q): the combined
     // north and diagonal links, and the plaquette alphas of both fields
     T cN = 0, c1 = 0, c2 = 0, cPD = 0, cPA = 0;
@@ -265,7 +276,15 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       }
       pNW = from_left(pN);
       pNE = from_right(pN);
-      if (P != 9) fN = M::tanh_(pN * isq2);  // phase 9's row r is past every use of phi
+      if constexpr (!kDiff) {
+        exC = exN; sxS = sxC; sxC = sxN; dNp = dN;
+        if constexpr (P < 8) {
+          exN = pNE - pNW;
+          sxN = (pNE - pN) + (pNW - pN);
+          dN = pN - pC;
+        }
+      }
+      if (P != 9) fN = M::phi(pN);  // phase 9's row r is past every use of phi
       if constexpr (P == 0) return;
       if constexpr (kAT == kAtFullShells && P >= 2) {
         pCE2 = from_right(pCE);
@@ -276,8 +295,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // fluxes are h J (gradients passed as h g)
       T FyN = T(0);
       if constexpr (!kDiff && P < 8)
-        FyN = aniso_flux<T, 1>(T(0.25) * (pNE + pCE - pNW - pCW), pN - pC, c.at_eps, rot_of(gC),
-                               c);
+        FyN = aniso_flux<T, 1>(T(0.25) * (exN + exC), dN, c.at_eps, rot_of(gC), c);
       // dynamic grains: the grain of row m at the next level (a liquid cell,
       // psi < 0, with a solid face neighbour takes the grain of the solid
       // neighbour with the largest psi, first of -x, +x, -y, +y on ties)
@@ -320,28 +338,30 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         const int m = r - 1;
         grain_next(m);
         const Rot2<T> R = rot_of(gC);
-        T dE = pCE - pC, dW = pCW - pC, dN = pN - pC, dS = pS - pC;
-        T s10 = dE + dW + dN + dS;
-        T s11 = (pNE - pC) + (pNW - pC) + (pSE - pC) + (pSW - pC);
-        T L = c.cL1 * s10 + c.cL2 * s11;
-        T ex = pCE - pCW, ey = pN - pS;
-        T e1 = pNE - pSW, e2 = pSE - pNW;
-        T G = c.cG1 * (ex * ex + ey * ey) + c.cG2 * (e1 * e1 + e2 * e2);
-        T ac = aniso_a(ex, ey, c.ac_eps, R, c);  // (ex, ey) = 2h g
-        T FxE = aniso_flux<T, 0>(dE, T(0.25) * (pN + pNE - pS - pSE), c.at_eps, R, c);
-        T FxW = from_left(FxE);
-        T ac2 = ac * ac;
-        T Nn = (FxE - FxW + FyN - FyS - ac2 * s10) * c.cStd;
-        T F1 = T(1), F2 = uC;
+        const T dd = dN - dNp;  // (pN - pC) + (pS - pC)
+        const T s10 = sxC + dd;
+        const T s11 = (sxN + sxS) + T(2) * dd;
+        const T ey = pN - pS;
+        const T e1 = pNE - pSW, e2 = pSE - pNW;
+        const T ac = aniso_a(exC, ey, c.ac_eps, R, c);  // (exC, ey) = 2h g
+        const T FxE = aniso_flux<T, 0>(pCE - pC, T(0.25) * (ey + from_right(ey)), c.at_eps, R, c);
+        const T FxW = from_left(FxE);
+        const T ac2 = ac * ac;
+        // h^2 times the right-hand side: ac^2 (L - sqrt2 phi G) with the
+        // standard Laplacian of the eps4 remainder (s10) taken off L, the
+        // face fluxes, and the bulk terms
+        const T lg = (c.rA1 * s10 + c.rA2 * s11) +
+                     fC * (c.rB1 * (exC * exC + ey * ey) + c.rB2 * (e1 * e1 + e2 * e2));
+        const T flux = (FxE - FxW) + (FyN - FyS);
+        T F1 = c.h2, F2 = uC;  // F1 times h^2
         if (kFrozen) {
-          T zeta = (T)(P >= 5 ? m : ghost_near(m, ny, a.bcy)) * c.h + off;
-          F1 = T(1) - c.omk * zeta * c.inv_lT;
-          F2 = uC + zeta * c.inv_lT;
+          const T zl = (T)(P >= 5 ? m : ghost_near(m, ny, a.bcy)) * c.hT + offT;  // zeta / lT
+          F1 = c.h2 - c.omkh2 * zl;
+          F2 = uC + zl;
         }
-        T ph = fC;
-        T omp = T(1) - ph * ph;
-        T rhs = ac2 * (L - sq2 * ph * G) + Nn + sq2 * (ph - c.lambda * omp * F2);
-        T rate = rhs * M::rcp(F1 * ac2);
+        const T omp = T(1) - fC * fC;
+        const T rhs = (ac2 * lg + flux) + c.rK * (fC - (c.lambda * omp) * F2);
+        const T rate = rhs * M::rcp(F1 * ac2);
         T aA = (T(1) + c.omk * uC) * omp * rate * T(0.5);
         if (P == 6 || ((P < 5 || P == 7) && a.bcx == PF_BC_NOFLUX)) {  // mirrored columns copy their image
           T fr = from_right(aA), fl = from_left(aA);
@@ -402,22 +422,25 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         // beta = U; field A alpha = alpha_A, beta = psi
         const int q = r - 2;
         T aq = c.D - c.D * fS, aq1 = c.D - c.D * fC;
-        T aE = from_right(aq), aNE = from_right(aq1);
-        T PD = (aq + aE + aq1 + aNE) * T(0.25);
-        T PDW = from_left(PD);
-        T uE = from_right(uS), uNE = from_right(uC), uNW = from_left(uC);
-        const T kE = aq + aE + PD + cPD, kN = aq + aq1 + PD + PDW;
-        const T gE = uE - uS, gN = uC - uS, gNE = uNE - uS, gNW = uNW - uS;
+        // link alphas carry a factor 4: the column sum t over rows q, q+1 gives
+        // the plaquette sum with one lane move, 4 abar_E = 4 (a + aE) + plaquettes
+        // above and below, 4 abar_N = 4 t + plaquettes right and left
+        const T t = aq + aq1;
+        const T PD = t + from_right(t);
+        const T PDW = from_left(PD);
+        const T kE = T(4) * (aq + from_right(aq)) + (PD + cPD), kN = T(4) * t + (PD + PDW);
+        const T gE = from_right(uS) - uS, gN = uC - uS;
+        const T gNE = from_right(uC) - uS, gNW = from_left(uC) - uS;
         T fE = kE * gE, fN = kN * gN;
         T d1 = PD * gNE, d2 = PDW * gNW;
 
         T PA = T(0);
         if constexpr (!kDiff) {
-          T bE = from_right(aAS), bNE = from_right(aAC);
-          PA = (aAS + bE + aAC + bNE) * T(0.25);
-          T PAW = from_left(PA);
-          T fEA = (aAS + bE + PA + cPA) * (pSE - pS);
-          T fNA = (aAS + aAC + PA + PAW) * (pC - pS);
+          const T tA = aAS + aAC;
+          PA = tA + from_right(tA);
+          const T PAW = from_left(PA);
+          T fEA = (T(4) * (aAS + from_right(aAS)) + (PA + cPA)) * (pSE - pS);
+          T fNA = (T(4) * tA + (PA + PAW)) * (pC - pS);
           T d1A = PA * (pCE - pS);
           T d2A = PAW * (pCW - pS);
           if constexpr (kAT == kAtFullShells) {
@@ -477,8 +500,8 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         }
 
         if constexpr (P >= 4) {
-          T div = c.cD1 * (fE - from_left(fE) + fN - cN) +
-                  c.cD2 * (d1 + d2 - from_left(c1) - from_right(c2));
+          T div = c.cD1 * ((fE - from_left(fE)) + (fN - cN)) +
+                  c.cD2 * ((d1 - from_left(c1)) + (d2 - from_right(c2)));
           // the held psi has no anti-trapping current and no source
           T rU = (kDiff ? div : div + sq2 * aAS) * M::rcp(T(1) + c.k - c.omk * fS);
           store_row(a.U_out + (size_t)q * (size_t)nx, nx, x, out_lane, uS + c.dt * rU);
@@ -559,8 +582,8 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // the pipeline computed from the same loads
       const int ms = a.shift_row - 1;
       if (ms >= y0 && ms < ye && ms <= ny - 2) {
-        const T f0 = M::tanh_(a.psi_in[prow(ms)] * isq2);
-        const T f1 = M::tanh_(a.psi_in[prow(ms + 1)] * isq2);
+        const T f0 = M::phi(a.psi_in[prow(ms)]);
+        const T f1 = M::phi(a.psi_in[prow(ms + 1)]);
         if (out_lane && f0 >= T(0) && f1 < T(0))
           over |= crossing_reaches(f0, f1, ms, a.shift_row, ythr, a.hd);
       }

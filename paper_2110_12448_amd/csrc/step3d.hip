@@ -190,7 +190,6 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
   const double ythr = (double)a.shift_row * a.hd;
   bool over = false;
   const T sq2 = T(1.4142135623730951);
-  const T isq2 = T(0.70710678118654752);
 
   auto rowoff = [&](int r) -> size_t {
     int j = ghost_near(r, ny, a.bcy);
@@ -303,7 +302,7 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
     auto form_fN = [&]() {
       T pNb = pN;
       if constexpr (kLatePhi) asm volatile("" : "+v"(pNb));
-      fN = M::tanh_(pNb * isq2);
+      fN = M::phi(pNb);
       if constexpr (kLatePhi) asm volatile("" : "+v"(fN));
     };
     auto publish_aD = [&]() { sm[oN + (kAD - kPsi) * RS] = c.D * (T(1) - fN); };
@@ -668,8 +667,8 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
   if (kReduce && out_wave) {
     const int ms = a.shift_row - 1;  // the row under the shift row
     if (ms >= y0 && ms < ye && ms <= ny - 2) {
-      const T f0 = M::tanh_(a.psi_in[pz + rowoff(ms)] * isq2);
-      const T f1 = M::tanh_(a.psi_in[pz + rowoff(ms + 1)] * isq2);
+      const T f0 = M::phi(a.psi_in[pz + rowoff(ms)]);
+      const T f1 = M::phi(a.psi_in[pz + rowoff(ms + 1)]);
       if (out_lane && f0 >= T(0) && f1 < T(0))
         over |= crossing_reaches(f0, f1, ms, a.shift_row, ythr, a.hd);
     }
