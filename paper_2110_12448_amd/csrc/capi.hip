@@ -397,6 +397,7 @@ Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, bool share, int min_seg = 1, int s
   a.nx = p.nx; a.ny = p.ny; a.bcx = p.bc[0]; a.bcy = p.bc[1];
   a.wout = g.wout; a.nstrips = g.nstrips; a.nsegs = g.nsegs;
   a.segbase = g.segbase; a.segrem = g.segrem;
+  a.strip_rcp = (unsigned)std::min<unsigned long long>((1ULL << 32) / g.nstrips, 0xffffffffULL);
   a.shared = g.shared;
   a.c = coef_of<T>(s);
   a.hd = p.h; a.y0 = p.y0; a.Vp = p.Vp; a.dtd = s->dt;

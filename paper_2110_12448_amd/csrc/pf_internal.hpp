@@ -83,6 +83,7 @@ struct Step2DArgs {
   T c2, s2;              // single grain: cos and sin of twice its angle
   int nx, ny, bcx, bcy;
   int wout, nstrips, nsegs, segbase, segrem;
+  unsigned strip_rcp;    // floor(2^32 / nstrips), at most 2^32 - 1
   int shared;            // waves of a workgroup share a strip and their junctions
   Coef<T> c;
   double hd, y0, Vp, dtd, inv_lTd;

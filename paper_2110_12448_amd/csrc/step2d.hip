@@ -154,8 +154,14 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
 
   if (wave < a.nstrips * a.nsegs) {
     // shared: nsegs is a multiple of 4, so every wave of the workgroup is here
-    const int strip = shared ? lb % a.nstrips : wave % a.nstrips;
-    const int segi = shared ? 4 * (lb / a.nstrips) + wv : wave / a.nstrips;
+    // (strip fastest; the quotient by the host's reciprocal, whose estimate
+    // is at most one too small: an integer division costs about 40
+    // instructions before the first load can be issued)
+    const unsigned n = shared ? (unsigned)lb : (unsigned)wave;
+    unsigned quo = __umulhi(n, a.strip_rcp);
+    if (n - quo * (unsigned)a.nstrips >= (unsigned)a.nstrips) ++quo;
+    const int strip = (int)(n - quo * (unsigned)a.nstrips);
+    const int segi = shared ? 4 * (int)quo + wv : (int)quo;
     const int x = strip * a.wout - 2 + lane;
     // x <= nx + 60: within one period unless the lattice is narrow
     const int gx = nx >= 62 ? ghost_near(x, nx, a.bcx) : ghost(x, nx, a.bcx);
@@ -172,19 +178,26 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     bool over = false;  // this lane saw a crossing at or above the shift row
     const T sq2 = T(1.4142135623730951);
 
-    auto prow = [&](int r) -> size_t {
-      int j = ghost_near(r, ny, a.bcy);
-      if (pend) j = min(j + 1, ny - 1);
-      return (size_t)j * (size_t)nx + (size_t)gx;
+    // stored row of lattice row r
+    auto row_of = [&](int r) -> int {
+      const int j = ghost_near(r, ny, a.bcy);
+      return pend ? min(j + 1, ny - 1) : j;
     };
     // the same for the steady state, whose rows (y0 + 5 .. ye + 1) can only
     // cross the top boundary, in plain arithmetic: no branch splits the row
-    const int top_per = a.bcy == PF_BC_PERIODIC ? ny : 0;
-    const int top_mir = a.bcy == PF_BC_PERIODIC ? 0 : 1;
-    auto prow_top = [&](int r) -> size_t {
-      const int over = max(r - (ny - 1), 0);  // 0, 1 or 2 rows past the top
-      const int j = r - top_per * min(over, 1) - top_mir * max(2 * over - 1, 0);
-      return (size_t)min(j + pend, ny - 1) * (size_t)nx + (size_t)gx;
+    const int top0 = a.bcy == PF_BC_PERIODIC ? 0 : ny - 1;
+    const int tops = a.bcy == PF_BC_PERIODIC ? 1 : -1;
+    auto row_top = [&](int r) -> int {
+      const int over = r - ny;  // 0 or 1 past the top
+      const int j = over < 0 ? r : top0 + tops * over;
+      return min(j + pend, ny - 1);
+    };
+    // psi, U (and grain) of stored row j at this lane's column
+    auto load = [&](int j, T &p, T &u, int &g) {
+      const size_t o = (size_t)j * (size_t)nx + (size_t)gx;
+      p = a.psi_in[o];
+      u = a.U_in[o];
+      if (kMulti) g = a.grain[o];
     };
     // a single grain's rotation and the coefficients read most per row live
     // in vector registers (see aniso_a)
@@ -224,13 +237,9 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     // last row read: one past the segment, or two for App. B's gradients on
     // the U row ye
     const int rl = ye + (kAT == kAtFullShells && !last ? 2 : 1);
-    {
-      size_t o0 = prow(rs), o1 = prow(rs + 1), o2 = prow(rs + 2);
-      lp0 = a.psi_in[o0]; lu0 = a.U_in[o0];
-      lp1 = a.psi_in[o1]; lu1 = a.U_in[o1];
-      lp2 = a.psi_in[o2]; lu2 = a.U_in[o2];
-      if (kMulti) { lg0 = a.grain[o0]; lg1 = a.grain[o1]; lg2 = a.grain[o2]; }
-    }
+    load(row_of(rs), lp0, lu0, lg0);
+    load(row_of(rs + 1), lp1, lu1, lg1);
+    load(row_of(rs + 2), lp2, lu2, lg2);
 
     // One row of the pipeline.  P is the pipeline phase: 0 loads only (row
     // y0-2), 1 adds the y face flux, 2 the psi rate of row y0-1, 3 the first
@@ -269,10 +278,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       if (P < 8 && (P >= 5 || r + 3 <= rl)) {
         // steady state: the last rows reload row rl (never consumed) instead
         // of branching around the load
-        size_t on = P >= 5 ? prow_top(min(r + 3, rl)) : prow(r + 3);
-        lp2 = a.psi_in[on];
-        lu2 = a.U_in[on];
-        if (kMulti) lg2 = a.grain[on];
+        load(P >= 5 ? row_top(min(r + 3, rl)) : row_of(r + 3), lp2, lu2, lg2);
       }
       pNW = from_left(pN);
       pNE = from_right(pN);
@@ -582,8 +588,8 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // the pipeline computed from the same loads
       const int ms = a.shift_row - 1;
       if (ms >= y0 && ms < ye && ms <= ny - 2) {
-        const T f0 = M::phi(a.psi_in[prow(ms)]);
-        const T f1 = M::phi(a.psi_in[prow(ms + 1)]);
+        const T f0 = M::phi(a.psi_in[(size_t)row_of(ms) * nx + gx]);
+        const T f1 = M::phi(a.psi_in[(size_t)row_of(ms + 1) * nx + gx]);
         if (out_lane && f0 >= T(0) && f1 < T(0))
           over |= crossing_reaches(f0, f1, ms, a.shift_row, ythr, a.hd);
       }
