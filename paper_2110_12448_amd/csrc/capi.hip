@@ -62,36 +62,56 @@ int default_seg2d(int nx, int ny, int precision, int ncu) {
 constexpr int kMinSegBatch2D = 8;
 constexpr size_t kMaxLds3DBytes = 163840;  // LDS one gfx950 workgroup may allocate
 constexpr size_t kMaxLds3D = kMaxLds3DBytes;
-// Default 3D geometry.  z rows per wide workgroup: 14 in FP32 (16 waves, the
-// most one workgroup holds: one workgroup per CU at the kernel's 100-128
-// VGPRs, ring rows costing 16/14), 6 in FP64 (8 waves, its launch bound:
-// two waves per SIMD at its ~230 VGPRs, ring rows costing 8/6).
-// Segments: the count that minimises the estimated time rounds x (rows + 2.5),
-// where rounds = ceil(workgroups / resident workgroups) and a segment's
-// prologue costs about 2.5 rows; the rows of a column are split evenly.  On
-// 256^3 FP32 (4 wide strips of 19 z tiles and a thin strip of 6) that is 3
-// segments of 85-86 rows (the thin strip 4 of 64), 252 workgroups in one
-// round; pf_autotune refines it per lattice.
+// Default 3D geometry.  z rows per wide workgroup: 14, 6 or 2 in FP32 (16, 8
+// or 4 waves; 16 is the most one workgroup holds, ring rows costing 16/14),
+// 6 or 2 in FP64 (its launch bound is 8 waves), with the segment count that
+// minimises the estimated time rounds x (rows + 2.5) x (1 + 0.43 w): rounds of
+// resident workgroups, a segment's prologue costing about 2.5 rows, and w
+// waves per SIMD on a CU of the fullest round (a row takes 1.8 us at one wave
+// per SIMD, 2.15 at two and 3.4 at four in FP32: on a lattice that leaves CUs
+// idle, more and smaller workgroups finish sooner).  The rows of a column are
+// split evenly.  Fewer z rows are taken only for 5% by that estimate, so that
+// large lattices keep the fewest ring rows: 256^3 FP32 (4 wide strips of 19 z
+// tiles and a thin strip of 6) takes 14 and 3 segments of 85-86 rows (the
+// thin strip 4 of 64), 252 workgroups in one round.  33x29x17 FP32: 28.6 us a
+// step with 14 z rows, 14.8 with 2; 64^3 26.1 and 18.7 with 6; 128^3 57.9
+// with 14 and 63.1 with 6.  pf_autotune refines it per lattice.
 std::pair<int, int> default_geom3d(const pf_params *p, int ncu) {
   const bool f64 = p->precision == PF_F64;
-  const int zt = std::min(f64 ? 6 : 14, std::max(1, p->nz));
-  const int nw = zt + 2;
-  const size_t lds = step3d_lds_bytes(p->nx, zt, f64 ? 8 : 4);
-  const int by_waves = std::max(1, (f64 ? 8 : 16) / nw);
-  const int by_lds = std::max(1, (int)(kMaxLds3DBytes / lds));
-  const long long resident = (long long)std::max(1, ncu) * std::min(by_waves, by_lds);
-  int best = p->ny;
+  const long long cus = std::max(1, ncu);
+  int best = p->ny, best_zt = 1;
   double best_cost = 1e300;
-  for (int n = 1; n <= std::max(1, p->ny / 4); ++n) {
-    const int rows = (p->ny + n - 1) / n;
-    const long long blocks = geom3d(p->nx, p->ny, p->nz, rows, zt).blocks;
-    const double cost = (double)((blocks + resident - 1) / resident) * (rows + 2.5);
-    if (cost < best_cost - 1e-9) {
-      best_cost = cost;
-      best = rows;
+  int last = 0;
+  for (int want : {14, 6, 2}) {
+    if (f64 && want > 6) continue;
+    const int zt = std::min(want, std::max(1, p->nz));
+    if (zt == last) continue;
+    last = zt;
+    const int nw = zt + 2;
+    const size_t lds = step3d_lds_bytes(p->nx, zt, f64 ? 8 : 4);
+    const int by_waves = std::max(1, (f64 ? 8 : 16) / nw);
+    const int by_lds = std::max(1, (int)(kMaxLds3DBytes / lds));
+    const long long per_cu = std::min(by_waves, by_lds);
+    int rows_zt = p->ny;
+    double cost_zt = 1e300;
+    for (int n = 1; n <= std::max(1, p->ny / 4); ++n) {
+      const int rows = (p->ny + n - 1) / n;
+      const long long blocks = geom3d(p->nx, p->ny, p->nz, rows, zt).blocks;
+      const long long rounds = (blocks + cus * per_cu - 1) / (cus * per_cu);
+      const double w = (double)(std::min(per_cu, (blocks + cus - 1) / cus) * nw) / 4.0;
+      const double cost = (double)rounds * (rows + 2.5) * (1.0 + 0.43 * w);
+      if (cost < cost_zt - 1e-9) {
+        cost_zt = cost;
+        rows_zt = rows;
+      }
+    }
+    if (cost_zt < 0.95 * best_cost) {
+      best_cost = cost_zt;
+      best = rows_zt;
+      best_zt = zt;
     }
   }
-  return {best, zt};
+  return {best, best_zt};
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -96,8 +96,9 @@ def estimated_waves(prob: dict, batched: bool = False, cus: int = 256) -> int:
     of the chip a solve fills.  60 output columns per wave; in 2D k =
     round(R^0.4) waves per SIMD with R = strips * ny / SIMDs, at most one
     segment per row, and inside a batch segments of that length but at least
-    8 rows; in 3D workgroups of 14 z rows in 16 waves (one per CU), with the
-    segment count that minimises rounds x (rows + 2.5)."""
+    8 rows; in 3D workgroups of 14, 6 or 2 z rows (16, 8 or 4 waves) with
+    the segment count that minimises rounds x (rows + 2.5) x (1 + 0.43 waves
+    per SIMD), as the library's default."""
     strips = -(-prob["nx"] // 60)
     if prob["dim"] == 2:
         ny, simds = prob["ny"], 4 * cus
@@ -107,15 +108,23 @@ def estimated_waves(prob: dict, batched: bool = False, cus: int = 256) -> int:
             nsegs = -(-ny // max(8, -(-ny // nsegs)))
         return strips * nsegs
     nx, ny, nz = prob["nx"], prob["ny"], prob["nz"]
-    zt = min(14, nz)
-    best, best_cost = ny, None
-    for n in range(1, max(1, ny // 4) + 1):
-        rows = -(-ny // n)
-        blocks = _geom3d_blocks(nx, ny, nz, rows, zt)
-        cost = -(-blocks // cus) * (rows + 2.5)
-        if best_cost is None or cost < best_cost - 1e-9:
-            best, best_cost = rows, cost
-    return _geom3d_blocks(nx, ny, nz, best, zt) * (zt + 2)
+    best, best_cost, last = 0, None, 0
+    for want in (14, 6, 2):
+        zt = min(want, nz)
+        if zt == last:
+            continue
+        last, nw, per_cu = zt, zt + 2, 16 // (zt + 2)
+        blocks_zt, cost_zt = 0, None
+        for n in range(1, max(1, ny // 4) + 1):
+            rows = -(-ny // n)
+            blocks = _geom3d_blocks(nx, ny, nz, rows, zt)
+            w = min(per_cu, -(-blocks // cus)) * nw / 4.0
+            cost = -(-blocks // (cus * per_cu)) * (rows + 2.5) * (1.0 + 0.43 * w)
+            if cost_zt is None or cost < cost_zt - 1e-9:
+                blocks_zt, cost_zt = blocks, cost
+        if best_cost is None or cost_zt < 0.95 * best_cost:
+            best, best_cost = blocks_zt * nw, cost_zt
+    return best
 
 
 def _work(r: Request) -> int:
