@@ -300,34 +300,27 @@ Coef<T> coef_of(const pf_solver *s) {
   c.an16 = (T)(16.0 * p.eps4);
   c.D = (T)p.D;
   c.lambda = (T)s->lambda;
-  c.inv_h = (T)(1.0 / h);
   c.h = (T)h;
-  c.cStd = (T)(1.0 / h2);
-  c.inv_lT = (T)(p.lT > 0.0 ? 1.0 / p.lT : 0.0);
+  // the psi equation times h^2, with L and G by their prefactors (2D: Eqs.
+  // 2D_L10, 2D_L01, Grad_10, Grad_11; 3D: Eqs. 3D_L100, 3D_L110, 3D_L111,
+  // Grad_100, Grad_110, Grad_111); the eps4 remainder holds -s1 / h^2
+  const double pl = p.dim == 2 ? 2.0 : 4.0, pg = p.dim == 2 ? 8.0 : 16.0;
+  c.rA1 = (T)(s->w[0] - 1.0);
+  c.rA2 = (T)(s->w[1] / pl);
+  c.rA3 = (T)(s->w[2] / pl);
+  c.rB1 = (T)(-sqrt(2.0) * s->w[0] / 4.0);
+  c.rB2 = (T)(-sqrt(2.0) * s->w[1] / pg);
+  c.rB3 = (T)(-sqrt(2.0) * s->w[2] / pg);
+  c.rK = (T)(sqrt(2.0) * h2);
+  c.h2 = (T)h2;
+  c.omkh2 = (T)((1.0 - p.k) * h2);
+  c.hT = (T)(p.lT > 0.0 ? h / p.lT : 0.0);
   if (p.dim == 2) {
-    // L_{1,0} = s10/h^2, L_{0,1} = s11/(2h^2) (Eqs. 2D_L10, 2D_L01)
-    c.cL1 = (T)(s->w[0] / h2);
-    c.cL2 = (T)(s->w[1] / (2.0 * h2));
-    c.cL3 = (T)0;
-    // G_{1,0} = (...)/(4h^2), G_{0,1} = (...)/(8h^2) (Eqs. Grad_10, Grad_11)
-    c.cG1 = (T)(s->w[0] / (4.0 * h2));
-    c.cG2 = (T)(s->w[1] / (8.0 * h2));
-    c.cG3 = (T)0;
-    // the psi equation times h^2 (its eps4 remainder holds -s10 / h^2)
-    c.rA1 = (T)(s->w[0] - 1.0);
-    c.rA2 = (T)(s->w[1] / 2.0);
-    c.rB1 = (T)(-sqrt(2.0) * s->w[0] / 4.0);
-    c.rB2 = (T)(-sqrt(2.0) * s->w[1] / 8.0);
-    c.rK = (T)(sqrt(2.0) * h2);
-    c.h2 = (T)h2;
-    c.omkh2 = (T)((1.0 - p.k) * h2);
-    c.hT = (T)(p.lT > 0.0 ? h / p.lT : 0.0);
     // D_{1,0}: fluxes carry the 4-point alpha sum, /(4h^2); D_{0,1}: plaquette
     // means times dbeta, /(2h^2) (Eqs. flux_10, flux_11); the kernel's link
     // alphas carry another factor 4
     c.cD1 = (T)(s->w[0] / (16.0 * h2));
     c.cD2 = (T)(s->w[1] / (8.0 * h2));
-    c.cD3 = (T)0;
     // two-point faces carry (alpha_0 + alpha_e) dbeta: /(2h^2); links of the
     // full current carry h / |h grad psi| and enter with a factor h
     c.cT = (T)(1.0 / (2.0 * h2));
@@ -337,26 +330,13 @@ Coef<T> coef_of(const pf_solver *s) {
     c.an2 = (T)(2.0 * p.eps4);
     c.an8 = (T)(8.0 * p.eps4);
   } else {
-    // L_{1,0,0} = s/h^2, L_{0,1,0} = s/(4h^2), L_{0,0,1} = s/(4h^2)
-    c.cL1 = (T)(s->w[0] / h2);
-    c.cL2 = (T)(s->w[1] / (4.0 * h2));
-    c.cL3 = (T)(s->w[2] / (4.0 * h2));
-    // G_{1,0,0} = /(4h^2), G_{0,1,0} = /(16h^2), G_{0,0,1} = /(16h^2)
-    c.cG1 = (T)(s->w[0] / (4.0 * h2));
-    c.cG2 = (T)(s->w[1] / (16.0 * h2));
-    c.cG3 = (T)(s->w[2] / (16.0 * h2));
-    // D_{1,0,0} = sum abar dbeta / h^2; D_{0,1,0}, D_{0,0,1} = / (4h^2)
-    c.cD1 = (T)(s->w[0] / h2);
-    c.cD2 = (T)(s->w[1] / (4.0 * h2));
-    c.cD3 = (T)(s->w[2] / (4.0 * h2));
-    c.k1a = (T)(s->w[0] / h2 / 4.0);
-    c.k1b = (T)(s->w[0] / h2 / 16.0);
-    c.k2a = (T)(s->w[1] / (4.0 * h2) * 3.0 / 16.0);
-    c.k2b = (T)(s->w[1] / (4.0 * h2) / 32.0);
-    c.k3 = (T)(s->w[2] / (4.0 * h2) / 8.0);
+    // D_{1,0,0} = sum abar dbeta / h^2; D_{0,1,0}, D_{0,0,1} = / (4h^2); the
+    // kernel's averages are 16, 32 and 8 times abar
+    c.kA = (T)(s->w[0] / h2 / 16.0);
+    c.kB = (T)(s->w[1] / (4.0 * h2) / 32.0);
+    c.kC = (T)(s->w[2] / (4.0 * h2) / 8.0);
     c.ac_eps = (T)(4e-12 * h2);
     c.f3_eps = (T)(16e-12 * h2);
-    c.f3_scale = (T)(1.0 / (4.0 * h2));
   }
   return c;
 }
@@ -476,6 +456,7 @@ int step_impl(pf_solver *s, long long nsteps, bool diffusion_only = false) {
     a.thin_nzt = g.thin_nzt; a.thin_segbase = g.thin_segbase; a.thin_segrem = g.thin_segrem;
     a.c = c;
     a.hd = p.h; a.y0 = p.y0; a.Vp = p.Vp; a.dtd = s->dt;
+    a.inv_lTd = p.lT > 0.0 ? 1.0 / p.lT : 0.0;
     a.frame = p.frame; a.shift_row = p.shift_row;
     for (long long i = 0; i < nsteps; ++i) {
       a.psi_in = field<T>(s, s->L.psi[s->cur]);

@@ -51,26 +51,19 @@ template <typename T>
 struct Coef {
   T dt, k, omk, eps4, D, lambda;
   T an0, an4, an16;  // 1 - 3 eps4, 4 eps4, 16 eps4 (cubic a_s and its torque)
-  T inv_h;          // 1/h
-  T cL1, cL2, cL3;  // shell weights of L over their prefactors
-  T cG1, cG2, cG3;  // shell weights of G over their prefactors
-  T cD1, cD2, cD3;  // shell weights of the divergence over their prefactors
-  T cStd;           // 1/h^2 (standard Laplacian of the eps4 remainder)
-  T inv_lT;         // 1/lT (frozen temperature)
+  T cD1, cD2;       // shell weights of the divergence over their prefactors (2D)
   T h;
   T cT;             // two-point <10> faces: 1/(2h^2) (2D)
   T at_eps;         // 1e-12 h^2: the |g|^2 <= 1e-12 guard for h g (face gradients, 2D)
   T ac_eps;         // 4e-12 h^2: the same guard for 2h g (centre differences)
   T an1, an2, an8;  // 1 + eps4, 2 eps4, 8 eps4 (2D a_s = 1 + eps4 cos 4t)
-  T rA1, rA2;       // h^2 times the shell weights of L, the standard Laplacian off the first (2D)
-  T rB1, rB2;       // -sqrt2 h^2 times the shell weights of G over their prefactors (2D)
-  T rK, h2, omkh2;  // sqrt2 h^2, h^2, (1 - k) h^2 (2D)
-  T hT;             // h / lT, 0 when isothermal (2D)
-  T k1a, k1b;       // cD1/4, cD1/16: <100> link alpha weights times the shell coefficient (3D)
-  T k2a, k2b;       // 3 cD2/16, cD2/32: the same for <110> links (3D)
-  T k3;             // cD3/8: <111> links, mean of the 8 cube corners (3D)
+  T rA1, rA2, rA3;  // h^2 times the shell weights of L over their prefactors, the
+                    // standard Laplacian taken off the first
+  T rB1, rB2, rB3;  // -sqrt2 h^2 times the shell weights of G over their prefactors
+  T rK, h2, omkh2;  // sqrt2 h^2, h^2, (1 - k) h^2
+  T hT;             // h / lT, 0 when isothermal
+  T kA, kB, kC;     // cD1/16, cD2/32, cD3/8: shell factors of the link sums (3D)
   T f3_eps;         // 16e-12 h^2: the |g|^2 <= 1e-12 guard for 4h g (face gradients, 3D)
-  T f3_scale;       // 1/(4 h^2): unscales the sum of the 4h-scaled face fluxes (3D)
 };
 
 template <typename T>
@@ -121,7 +114,7 @@ struct Step3DArgs {
   int thin_g, thin_G, thin_wout;  // thin strip: lane groups per wave, lanes per group, width
   int thin_nzt, thin_segbase, thin_segrem;  // its z tiles and segments
   Coef<T> c;
-  double hd, y0, Vp, dtd;
+  double hd, y0, Vp, dtd, inv_lTd;
   long long step;
   int frame, shift_row;
   const FrameState *frame_in;

@@ -55,8 +55,9 @@ struct Rot3 {
 template <typename T, int comp>
 __device__ __forceinline__ T aniso3(T gx, T gy, T gz, const Rot3<T> &R, const Coef<T> &c,
                                     T eps) {
+  // (below the guard r2 may be inf: the selects drop what it feeds)
   T g2 = gx * gx + gy * gy + gz * gz;
-  T r2 = Math<T>::rcp(g2 > eps ? g2 : eps);
+  T r2 = Math<T>::rcp(g2);
   T c0 = R.m[0] * gx + R.m[3] * gy + R.m[6] * gz;
   T c1 = R.m[1] * gx + R.m[4] * gy + R.m[7] * gz;
   T c2 = R.m[2] * gx + R.m[5] * gy + R.m[8] * gz;
@@ -92,12 +93,15 @@ __host__ __device__ constexpr int nb(int dx, int dy, int dz) {
 constexpr int kRS = 66;  // LDS row stride: lane l at l + 1, pads at 0 and 65
 enum LdsField { kPsi = 0, kU = 1, kAD = 2, kAA = 3 };  // alpha_D = D~ (1 - phi), alpha_A
 
-// alpha averages of the links a cell owns, times their shell coefficient
-// (Eqs. divergence_100, divergence_110): <100> links abar = P(0) + P(d) with
-// P = alpha/4 + (sum of the 4 neighbours across the link axis)/16; <110>
-// links abar = 3/16 (in-plane plaquette) + 1/32 (the two plaquettes beside
-// it along the third axis).  Py1 is P_y of the cell one row up, carried.
-// <111> links (sx, +1, sz): abar = mean of the 8 corners of the cube.
+// alpha averages of the links a cell owns (Eqs. divergence_100,
+// divergence_110), as sums with whole-number weights: <100> links carry 16
+// abar = P(0) + P(d) with P = 4 alpha + (sum of the 4 neighbours across the
+// link axis); <110> links 32 abar = 6 (in-plane plaquette) + (the two
+// plaquettes beside it along the third axis); <111> links (sx, +1, sz) 8 abar
+// = the 8 corners of the cube.  The shells' factors (kA, kB, kC) multiply the
+// sums of link values: a coefficient in each average was an SGPR operand,
+// which halves an FP32 instruction's issue rate.  Py1 is P_y of the cell one
+// row up, carried.
 template <typename T>
 struct Abar9 {
   T E, N, Up, NE, NW, EU, WU, NU, ND, Py1;
@@ -148,8 +152,10 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
   // so that the four fields of one (row, layer) sit at fixed offsets from one
   // another and share one address computation.
   T *XL = sm + 4 * 5 * SLOT;  // link exchange [row parity][to above, to below][z row][lane]
-  T *FZ = XL + 4 * NW * GL;   // z-up face flux of each z row [z row][lane]
-  int8_t *gL = reinterpret_cast<int8_t *>(FZ + NW * GL);  // grains, 5 row slots
+  // z-up face flux of each z row [z row + 1][lane]; the first is the lowest
+  // row's own z-down flux
+  T *FZ = XL + 4 * NW * GL;
+  int8_t *gL = reinterpret_cast<int8_t *>(FZ + (NW + 1) * GL);  // grains, 5 row slots
 
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int lane = threadIdx.x & 63;
@@ -185,12 +191,20 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
 
   const int pend = a.frame ? a.frame_in->pending : 0;
   const long long shift = a.frame ? a.frame_in->base + pend : 0;
-  T off = T(0);
-  if (kFrozen) off = (T)((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd));
+  T offT = T(0);  // zeta / lT of row 0
+  if (kFrozen)
+    offT = (T)(((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd)) * a.inv_lTd);
   const double ythr = (double)a.shift_row * a.hd;
   bool over = false;
   const T sq2 = T(1.4142135623730951);
 
+  // row index of lattice row r >= 0 in scalar arithmetic without a branch
+  const int top0 = a.bcy == PF_BC_PERIODIC ? 0 : ny - 1;
+  const int tops = a.bcy == PF_BC_PERIODIC ? 1 : -1;
+  auto row_up = [&](int r) -> int {
+    const int over = r - ny;
+    return over < 0 ? r : top0 + tops * over;
+  };
   auto rowoff = [&](int r) -> size_t {
     int j = ghost_near(r, ny, a.bcy);
     if (pend) j = min(j + 1, ny - 1);
@@ -265,12 +279,15 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
 
   // U of the waiting row qf from its own part and the neighbours' links
   // (output rows only: their neighbours zr - 1 and zr + 1 exist in the tile)
-  auto finalize = [&](int qf) {
-    if (!out_wave) return;
-    const int par = qf & 1;
-    const T below = XL[((par * 2 + 0) * NW + (zr - 1)) * GL + lx];
-    const T above = XL[((par * 2 + 1) * NW + (zr + 1)) * GL + lx];
-    store_row(a.U_out + (pz - (size_t)gx) + (size_t)qf * nx, nx, x, out_lane,
+  // (the ring rows read a row of their own and store nothing; ok: the row is
+  // one of the segment's)
+  const int xlb = max(zr - 1, 0) * GL + lx, xla = (NW + min(zr + 1, NW - 1)) * GL + lx;
+  const size_t pzr = pz - (size_t)gx;
+  auto finalize = [&](int qf, bool ok) {
+    const int par = (qf & 1) * 2 * NW * GL;
+    const T below = XL[par + xlb];
+    const T above = XL[par + xla];
+    store_row(a.U_out + pzr + (size_t)max(qf, 0) * nx, nx, x, ok & out_wave & out_lane,
                waitU + c.dt * waitDen * (waitBase - below - above));
   };
 
@@ -283,7 +300,8 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
     {
       // the last iteration reloads row ye + 1 (never consumed) rather than
       // branching around the loads
-      size_t ro = rowoff(min(r + 1, ye + 1));
+      size_t ro = P == 4 ? (size_t)min(row_up(min(r + 1, ye + 1)) + pend, ny - 1) * (size_t)nx
+                         : rowoff(min(r + 1, ye + 1));
       nxt_p = a.psi_in[pz + ro];
       nxt_u = a.U_in[pz + ro];
       if (ring) nxt_h = a.psi_in[pzh + ro];
@@ -376,32 +394,18 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
           }
       if constexpr (kLatePhi) form_fN();
       const T p0 = Pn[nb(0, 0, 0)];
-      T s1 = T(0), s2 = T(0), s3 = T(0);
-      T g1 = T(0), g2 = T(0), g3 = T(0);
-#pragma unroll
-      for (int dz = -1; dz <= 1; ++dz)
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-          for (int dx = -1; dx <= 1; ++dx) {
-            const int sh = (dx != 0) + (dy != 0) + (dz != 0);
-            if (sh == 0 || (sh == 3 && !kShell3)) continue;
-            T d = Pn[nb(dx, dy, dz)] - p0;
-            if (sh == 1) s1 += d; else if (sh == 2) s2 += d; else s3 += d;
-            // gradient-square pairs: one term per opposite pair (first
-            // non-zero offset positive)
-            const int first = dx != 0 ? dx : (dy != 0 ? dy : dz);
-            if (first > 0) {
-              T e = Pn[nb(dx, dy, dz)] - Pn[nb(-dx, -dy, -dz)];
-              if (sh == 1) g1 += e * e; else if (sh == 2) g2 += e * e; else g3 += e * e;
-            }
-          }
-      T Lap = c.cL1 * s1 + c.cL2 * s2;
-      T G = c.cG1 * g1 + c.cG2 * g2;
-      if constexpr (kShell3) {
-        Lap += c.cL3 * s3;
-        G += c.cG3 * g3;
-      }
+      auto dif = [&](int dx, int dy, int dz) -> T { return Pn[nb(dx, dy, dz)] - p0; };
+      auto opp = [&](int dx, int dy, int dz) -> T {  // difference of an opposite pair
+        return Pn[nb(dx, dy, dz)] - Pn[nb(-dx, -dy, -dz)];
+      };
+      const T s1 = ((dif(-1, 0, 0) + dif(1, 0, 0)) + (dif(0, -1, 0) + dif(0, 1, 0))) +
+                   (dif(0, 0, -1) + dif(0, 0, 1));
+      const T s2 = (((dif(-1, -1, 0) + dif(1, 1, 0)) + (dif(-1, 1, 0) + dif(1, -1, 0))) +
+                    ((dif(0, -1, -1) + dif(0, 1, 1)) + (dif(0, -1, 1) + dif(0, 1, -1)))) +
+                   ((dif(-1, 0, -1) + dif(1, 0, 1)) + (dif(-1, 0, 1) + dif(1, 0, -1)));
+      const T e1 = opp(1, 1, 0), e2 = opp(1, -1, 0), e3 = opp(0, 1, 1), e4 = opp(0, 1, -1);
+      const T e5 = opp(1, 0, 1), e6 = opp(1, 0, -1);
+      const T g2 = e1 * e1 + e2 * e2 + e3 * e3 + e4 * e4 + e5 * e5 + e6 * e6;
       const Rot3<T> R = rot_of(gC);
       // central differences (2h g at the centre); the face gradients below
       // are 4h g: the normal difference times 4 and, for each tangential
@@ -409,6 +413,19 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       const T cx = Pn[nb(1, 0, 0)] - Pn[nb(-1, 0, 0)];
       const T cy = Pn[nb(0, 1, 0)] - Pn[nb(0, -1, 0)];
       const T cz = Pn[nb(0, 0, 1)] - Pn[nb(0, 0, -1)];
+      const T g1 = cx * cx + cy * cy + cz * cz;
+      // h^2 (L - sqrt2 phi G), the standard Laplacian s1 / h^2 of the eps4
+      // remainder taken off L
+      T lap = c.rA1 * s1 + c.rA2 * s2;
+      T grd = c.rB1 * g1 + c.rB2 * g2;
+      if constexpr (kShell3) {
+        const T s3 = ((dif(-1, -1, -1) + dif(1, 1, 1)) + (dif(-1, -1, 1) + dif(1, 1, -1))) +
+                     ((dif(-1, 1, -1) + dif(1, -1, 1)) + (dif(-1, 1, 1) + dif(1, -1, -1)));
+        const T e7 = opp(1, 1, 1), e8 = opp(1, 1, -1), e9 = opp(1, -1, 1), e10 = opp(1, -1, -1);
+        lap += c.rA3 * s3;
+        grd += c.rB3 * (e7 * e7 + e8 * e8 + e9 * e9 + e10 * e10);
+      }
+      const T lg = lap + fC * grd;
       T ac = aniso3<T, -1>(cx, cy, cz, R, c, c.ac_eps);
       // x face east of the cell (the right lane's differences by DPP)
       T FxE = aniso3<T, 0>(T(4) * (Pn[nb(1, 0, 0)] - p0), cy + from_right(cy),
@@ -424,31 +441,29 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       T FzU = aniso3<T, 2>(cx + (Pn[nb(1, 0, 1)] - Pn[nb(-1, 0, 1)]),
                            cy + (Pn[nb(0, 1, 1)] - Pn[nb(0, -1, 1)]),
                            T(4) * (Pn[nb(0, 0, 1)] - p0), R, c, c.f3_eps);
-      FZ[zr * GL + lx] = FzU;
-      T FzD;
+      FZ[(zr + 1) * GL + lx] = FzU;
       if (w == 0) {
         Rot3<T> Rd = R;
         if (kMulti) Rd = rot_of(a.grain[pzd + rowoff(m)]);
-        FzD = aniso3<T, 2>((Pn[nb(1, 0, -1)] - Pn[nb(-1, 0, -1)]) + cx,
+        const T fzd = aniso3<T, 2>((Pn[nb(1, 0, -1)] - Pn[nb(-1, 0, -1)]) + cx,
                            (Pn[nb(0, 1, -1)] - Pn[nb(0, -1, -1)]) + cy,
                            T(4) * (p0 - Pn[nb(0, 0, -1)]), Rd, c, c.f3_eps);
+        if (zr == 0) FZ[lx] = fzd;
       }
       __syncthreads();
-      if (zr != 0) FzD = FZ[(zr - 1) * GL + lx];
+      const T FzD = FZ[zr * GL + lx];
       const T ac2 = ac * ac;
-      // the standard Laplacian of the remainder is the <100> sum s1 / h^2
-      T Nn = (FxE - FxW + FyN - FyS + FzU - FzD) * c.f3_scale - ac2 * (s1 * c.cStd);
+      const T flux = (FxE - FxW) + (FyN - FyS) + (FzU - FzD);  // 4 h^2 times the divergence
       FyS = FyN;
-      T F1 = T(1), F2 = uC;
+      T F1 = c.h2, F2 = uC;  // F1 times h^2
       if (kFrozen) {
-        T zeta = (T)ghost_near(m, ny, a.bcy) * c.h + off;
-        F1 = T(1) - c.omk * zeta * c.inv_lT;
-        F2 = uC + zeta * c.inv_lT;
+        const T zl = (T)(P == 4 ? row_up(m) : ghost_near(m, ny, a.bcy)) * c.hT + offT;  // zeta/lT
+        F1 = c.h2 - c.omkh2 * zl;
+        F2 = uC + zl;
       }
-      const T ph = fC;
-      const T omp = T(1) - ph * ph;
-      T rhs = ac2 * (Lap - sq2 * ph * G) + Nn + sq2 * (ph - c.lambda * omp * F2);
-      T rate = rhs * M::rcp(F1 * ac2);
+      const T omp = T(1) - fC * fC;
+      const T rhs = (ac2 * lg + T(0.25) * flux) + c.rK * (fC - (c.lambda * omp) * F2);
+      const T rate = rhs * M::rcp(F1 * ac2);
       T aA = (T(1) + c.omk * uC) * omp * rate * T(0.5);
       if (a.bcx == PF_BC_NOFLUX) {  // mirrored columns take their image's value
         T fr = from_right(aA), fl = from_left(aA);
@@ -486,13 +501,14 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
             a.grain_out[pz + (size_t)m * nx - (size_t)gx + (size_t)x] = (int8_t)gn;
         }
       }
-      if (P >= 3 && m < ye && out_wave) {
-        store_row(a.psi_out + (pz - (size_t)gx) + (size_t)m * nx, nx, x, out_lane, pC + c.dt * rate);
+      if constexpr (P >= 3) {
+        store_row(a.psi_out + pzr + (size_t)m * nx, nx, x, (m < ye) & out_wave & out_lane,
+                  pC + c.dt * rate);
         // moving-frame vote as a mask: rows at or above the shift row
         // qualify outright; the crossing height of the row under it is
         // taken in FP64 once, after the rows
         if (kReduce)
-          over = over | (out_lane & (m >= a.shift_row) & (m <= ny - 2) & (fC >= T(0)) & (fN < T(0)));
+          over = over | (out_lane & out_wave & (m < ye) & (m >= a.shift_row) & (m <= ny - 2) & (fC >= T(0)) & (fN < T(0)));
       }
     }
     // ---------------- phase C's operands that this iteration's alpha_A does
@@ -523,21 +539,21 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       const T a00 = rd(AL, 0, 0, 0), a10 = rd(AL, 1, 0, 0);
       const T a0m = rd(AL, 0, -1, 0), a0p = rd(AL, 0, 1, 0);
       const T a1m = rd(AL, 1, -1, 0), a1p = rd(AL, 1, 1, 0);
-      o.Py1 = c.k1a * a10 + c.k1b * (rd(AL, 1, 0, -1) + rd(AL, 1, 0, 1) + a1m + a1p);
+      o.Py1 = T(4) * a10 + ((rd(AL, 1, 0, -1) + rd(AL, 1, 0, 1)) + (a1m + a1p));
       o.N = Pyq + o.Py1;
       // xy plaquettes {x, x+1} x {q, q+1} at z-1, z, z+1
       const T cm = a0m + a1m, c0 = a00 + a10, cp = a0p + a1p;
       const T Xm = cm + from_right(cm), X0 = c0 + from_right(c0), Xp = cp + from_right(cp);
-      o.NE = c.k2a * X0 + c.k2b * (Xm + Xp);
+      o.NE = T(6) * X0 + (Xm + Xp);
       o.NW = from_left(o.NE);
       // yz plaquettes {q, q+1} x {z, z+1} (NU) and {z-1, z} (ND) at x-1, x, x+1
       const T S = c0 + cp, Sd = cm + c0;
-      o.NU = c.k2a * S + c.k2b * (from_left(S) + from_right(S));
-      o.ND = c.k2a * Sd + c.k2b * (from_left(Sd) + from_right(Sd));
+      o.NU = T(6) * S + (from_left(S) + from_right(S));
+      o.ND = T(6) * Sd + (from_left(Sd) + from_right(Sd));
       if constexpr (kShell3) {
         // the cube {x, x+1} x {q, q+1} x {z, z+1} is two stacked plaquettes
-        o.Tpp = c.k3 * (X0 + Xp);
-        o.Tpm = c.k3 * (X0 + Xm);
+        o.Tpp = X0 + Xp;
+        o.Tpm = X0 + Xm;
         o.Tmp = from_left(o.Tpp);
         o.Tmm = from_left(o.Tpm);
       } else {
@@ -545,15 +561,16 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       }
       if constexpr (kFull) {
         const T am0 = rd(AL, -1, 0, 0), am1 = rd(AL, -1, 1, 0);
-        const T Px = c.k1a * a00 + c.k1b * (am0 + a10 + a0m + a0p);
+        const T yy = am0 + a10;
+        const T Px = T(4) * a00 + (yy + (a0m + a0p));
         o.E = Px + from_right(Px);
-        const T Pz0 = c.k1a * a00 + c.k1b * (rd(AL, 0, 0, -1) + rd(AL, 0, 0, 1) + am0 + a10);
-        const T Pz1 = c.k1a * a0p + c.k1b * (rd(AL, 0, 1, -1) + rd(AL, 0, 1, 1) + am1 + a1p);
+        const T Pz0 = T(4) * a00 + ((rd(AL, 0, 0, -1) + rd(AL, 0, 0, 1)) + yy);
+        const T Pz1 = T(4) * a0p + ((rd(AL, 0, 1, -1) + rd(AL, 0, 1, 1)) + (am1 + a1p));
         o.Up = Pz0 + Pz1;
         // xz plaquettes {x, x+1} x {z, z+1} at q-1, q, q+1
         const T ym = am0 + am1, y0s = a00 + a0p, yp = a10 + a1p;
         const T Ym = ym + from_right(ym), Y0 = y0s + from_right(y0s), Yp = yp + from_right(yp);
-        o.EU = c.k2a * Y0 + c.k2b * (Ym + Yp);
+        o.EU = T(6) * Y0 + (Ym + Yp);
         o.WU = from_left(o.EU);
       } else {
         o.E = o.Up = o.EU = o.WU = T(0);
@@ -588,8 +605,8 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
     };
     // P_y of row q itself: carried from the row below except at the start
     auto py_here = [&](int AL) -> T {
-      return c.k1a * rd(AL, 0, 0, 0) +
-             c.k1b * (rd(AL, 0, 0, -1) + rd(AL, 0, 0, 1) + rd(AL, 0, -1, 0) + rd(AL, 0, 1, 0));
+      return T(4) * rd(AL, 0, 0, 0) +
+             ((rd(AL, 0, 0, -1) + rd(AL, 0, 0, 1)) + (rd(AL, 0, -1, 0) + rd(AL, 0, 1, 0)));
     };
     Diff9<T> dU{}, dP{};
     Abar9<T> bD{};
@@ -633,21 +650,27 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
         const T fEU = bD.EU * dU.EU + bA.EU * dP.EU;
         const T fWU = bD.WU * dU.WU + bA.WU * dP.WU;
         // links the waves above and below take with the opposite sign
-        const int par = q & 1;
-        XL[((par * 2 + 0) * NW + zr) * GL + lx] = fUp + from_left(fEU) + from_right(fWU) + NUprev;
-        XL[((par * 2 + 1) * NW + zr) * GL + lx] = NDprev;
-        T own = ((fE + fN_) + (fUp + fNE)) + ((fNW + fEU) + (fWU + fNU)) + fND + f111;
-        T part = own - from_left(fE) - southSum;
+        const int par = (q & 1) * 2 * NW * GL + zr * GL + lx;
+        XL[par] = c.kA * fUp + (c.kB * (from_left(fEU) + from_right(fWU)) + NUprev);
+        XL[par + NW * GL] = NDprev;
+        const T own1 = ((fE + fN_) + fUp) - from_left(fE);
+        const T own2 = ((fNE + fNW) + (fEU + fWU)) + (fNU + fND);
+        T own = c.kA * own1 + (c.kB * own2 - southSum);
+        if constexpr (kShell3) own += c.kC * f111;
         // finish the row below with its neighbours' links (published one
         // iteration ago), then let row q wait
-        if (q - 1 >= y0) finalize(q - 1);
+        finalize(q - 1, q - 1 >= y0);
         waitU = uS;
-        waitBase = part + sq2 * aAq;
+        waitBase = own + sq2 * aAq;
         waitDen = M::rcp(T(1) + c.k - c.omk * fS);
       }
-      southSum = fN_ + from_left(fNE) + from_right(fNW);
-      NUprev = fNU + up111;
-      NDprev = fND + dn111;
+      southSum = c.kA * fN_ + c.kB * (from_left(fNE) + from_right(fNW));
+      NUprev = c.kB * fNU;
+      NDprev = c.kB * fND;
+      if constexpr (kShell3) {
+        NUprev += c.kC * up111;
+        NDprev += c.kC * dn111;
+      }
     }
   };
   using I0 = std::integral_constant<int, 0>;
@@ -662,7 +685,7 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
   for (int r = y0 + 2; r <= ye + 1; ++r) iter(I4{}, r);
   // the last row's neighbours published their links in the last iteration
   __syncthreads();
-  finalize(ye - 1);
+  finalize(ye - 1, true);
 
   if (kReduce && out_wave) {
     const int ms = a.shift_row - 1;  // the row under the shift row
@@ -767,12 +790,12 @@ size_t step3d_lds_bytes(int nx, int ztile, size_t elem) {
   // and a thin tile's
   const Geom3D g = geom3d(nx, 8, 8, 8, ztile);
   const size_t nw = (size_t)g.ztile + 2;
-  size_t wide = ((size_t)20 * (nw + 2) * (size_t)kRS + (size_t)5 * nw * 64) * elem +
+  size_t wide = ((size_t)20 * (nw + 2) * (size_t)kRS + (size_t)(5 * nw + 1) * 64) * elem +
                 (((size_t)5 * (nw + 2) * (size_t)kRS + 15) & ~(size_t)15);
   size_t thin = 0;
   if (g.thin_g > 0) {
     const size_t NW = nw * (size_t)g.thin_g, RS = (size_t)g.thin_G + 2;
-    thin = ((size_t)20 * (NW + 2) * RS + (size_t)5 * NW * (size_t)g.thin_G) * elem +
+    thin = ((size_t)20 * (NW + 2) * RS + (5 * NW + 1) * (size_t)g.thin_G) * elem +
            (((size_t)5 * (NW + 2) * RS + 15) & ~(size_t)15);
   }
   return wide > thin ? wide : thin;
@@ -807,7 +830,7 @@ hipError_t launch_step3d(const Step3DArgs<T> &a, const Geom3D &g, bool frozen, b
                          bool multi, hipStream_t st) {
   dim3 grid(g.blocks), block(g.threads);
   size_t lds = step3d_lds_bytes(a.nx, g.ztile, sizeof(T));
-  const bool shell3 = a.c.cD3 != T(0) || a.c.cL3 != T(0) || a.c.cG3 != T(0);
+  const bool shell3 = a.c.kC != T(0);
   hipError_t e = hipSuccess;
 #define PF_L3(F, R, MU, S3) e = launch3<T, F, R, MU, S3>(a, grid, block, lds, st)
 #define PF_L3S(F, R, MU) \
