@@ -71,10 +71,13 @@ struct Rot2 {
 // instruction with an SGPR operand issues at half the rate of one without
 // (4.9 against 2.7 cycles a wave measured at 4 waves per SIMD), as do lane
 // moves, compares and selects.
-template <typename T>
+template <typename T, bool kPause>
 __device__ __forceinline__ T aniso_a(T gx, T gy, T g2eps, const Rot2<T> &R, const Coef<T> &c) {
   const T g2 = gx * gx + gy * gy, d = gx * gx - gy * gy, p2 = (gx + gx) * gy;
-  const T wn = (R.c2 * p2 - R.s2 * d) * Math<T>::rcp(g2);
+  T w = R.c2 * p2 - R.s2 * d;
+  pause_issue<kPause>(w);
+  T wn = w * Math<T>::rcp(g2);
+  pause_issue<kPause>(wn);
   const T a = c.an1 - (c.an2 * wn) * wn;  // 1 + eps4 - 2 eps4 sin^2 2t
   return g2 > g2eps ? a : T(1);
 }
@@ -83,16 +86,20 @@ __device__ __forceinline__ T aniso_a(T gx, T gy, T g2eps, const Rot2<T> &R, cons
 // J = a^2 g + |g|^2 a da/dg.  In 2D the second term is a (da/dt) g_perp,
 // g_perp = (-gy, gx), with da/dt = -8 eps4 sin 2t cos 2t.  Below the guard
 // the normalisation 1/|g|^2 is taken as 0, which leaves a = 1 and J = g.
-template <typename T, int comp>
+template <typename T, int comp, bool kPause>
 __device__ __forceinline__ T aniso_flux(T gx, T gy, T g2eps, const Rot2<T> &R,
                                         const Coef<T> &c) {
   const T g2 = gx * gx + gy * gy, d = gx * gx - gy * gy, p2 = (gx + gx) * gy;
   const T rg = Math<T>::rcp(g2);
   const T r2 = g2 > g2eps ? rg : T(0);
-  const T wn = (R.c2 * p2 - R.s2 * d) * r2;
-  const T vn = (R.c2 * d + R.s2 * p2) * r2;
+  T w = R.c2 * p2 - R.s2 * d;
+  pause_issue<kPause>(w);
+  T wn = w * r2;
+  T vn = (R.c2 * d + R.s2 * p2) * r2;
+  pause_issue<kPause>(vn);
   const T a = T(1) + c.eps4 * (vn * vn - wn * wn);
-  const T ath = (c.an8 * wn) * vn;  // -da/dt
+  T ath = (c.an8 * wn) * vn;  // -da/dt
+  pause_issue<kPause>(ath);
   return comp == 0 ? a * (a * gx + ath * gy) : a * (a * gy - ath * gx);
 }
 
@@ -258,6 +265,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     };
     auto iter = [&](auto phase, int r) {
       constexpr int P = decltype(phase)::value;
+      constexpr bool kPause = P == 5 || P == 6;
       if constexpr (kAT == kAtFullShells) {
         pB2 = pB1; pB2E = pB1E; pB1E2 = pSE2;
         pSE2 = pCE2; pSW2 = pCW2;
@@ -287,6 +295,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         if constexpr (P < 8) {
           exN = pNE - pNW;
           sxN = (pNE - pN) + (pNW - pN);
+          pause_issue<kPause>(sxN);
           dN = pN - pC;
         }
       }
@@ -301,7 +310,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // fluxes are h J (gradients passed as h g)
       T FyN = T(0);
       if constexpr (!kDiff && P < 8)
-        FyN = aniso_flux<T, 1>(T(0.25) * (exN + exC), dN, c.at_eps, rot_of(gC), c);
+        FyN = aniso_flux<T, 1, kPause>(T(0.25) * (exN + exC), dN, c.at_eps, rot_of(gC), c);
       // dynamic grains: the grain of row m at the next level (a liquid cell,
       // psi < 0, with a solid face neighbour takes the grain of the solid
       // neighbour with the largest psi, first of -x, +x, -y, +y on ties)
@@ -346,18 +355,21 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         const Rot2<T> R = rot_of(gC);
         const T dd = dN - dNp;  // (pN - pC) + (pS - pC)
         const T s10 = sxC + dd;
-        const T s11 = (sxN + sxS) + T(2) * dd;
-        const T ey = pN - pS;
+        T s11 = (sxN + sxS) + T(2) * dd;
+        pause_issue<kPause>(s11);
+        T ey = pN - pS;
+        pause_issue<kPause>(ey);
         const T e1 = pNE - pSW, e2 = pSE - pNW;
-        const T ac = aniso_a(exC, ey, c.ac_eps, R, c);  // (exC, ey) = 2h g
-        const T FxE = aniso_flux<T, 0>(pCE - pC, T(0.25) * (ey + from_right(ey)), c.at_eps, R, c);
+        const T ac = aniso_a<T, kPause>(exC, ey, c.ac_eps, R, c);  // (exC, ey) = 2h g
+        const T FxE = aniso_flux<T, 0, kPause>(pCE - pC, T(0.25) * (ey + from_right(ey)), c.at_eps, R, c);
         const T FxW = from_left(FxE);
         const T ac2 = ac * ac;
         // h^2 times the right-hand side: ac^2 (L - sqrt2 phi G) with the
         // standard Laplacian of the eps4 remainder (s10) taken off L, the
         // face fluxes, and the bulk terms
-        const T lg = (c.rA1 * s10 + c.rA2 * s11) +
+        T lg = (c.rA1 * s10 + c.rA2 * s11) +
                      fC * (c.rB1 * (exC * exC + ey * ey) + c.rB2 * (e1 * e1 + e2 * e2));
+        pause_issue<kPause>(lg);
         const T flux = (FxE - FxW) + (FyN - FyS);
         T F1 = c.h2, F2 = uC;  // F1 times h^2
         if (kFrozen) {
@@ -365,8 +377,10 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
           F1 = c.h2 - c.omkh2 * zl;
           F2 = uC + zl;
         }
-        const T omp = T(1) - fC * fC;
-        const T rhs = (ac2 * lg + flux) + c.rK * (fC - (c.lambda * omp) * F2);
+        T omp = T(1) - fC * fC;
+        pause_issue<kPause>(omp);
+        T rhs = (ac2 * lg + flux) + c.rK * (fC - (c.lambda * omp) * F2);
+        pause_issue<kPause>(rhs);
         const T rate = rhs * M::rcp(F1 * ac2);
         T aA = (T(1) + c.omk * uC) * omp * rate * T(0.5);
         if (P == 6 || ((P < 5 || P == 7) && a.bcx == PF_BC_NOFLUX)) {  // mirrored columns copy their image
@@ -431,22 +445,32 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         // link alphas carry a factor 4: the column sum t over rows q, q+1 gives
         // the plaquette sum with one lane move, 4 abar_E = 4 (a + aE) + plaquettes
         // above and below, 4 abar_N = 4 t + plaquettes right and left
-        const T t = aq + aq1;
-        const T PD = t + from_right(t);
+        T t = aq + aq1;
+        pause_issue<kPause>(t);
+        T PD = t + from_right(t);
+        pause_issue<kPause>(PD);
         const T PDW = from_left(PD);
-        const T kE = T(4) * (aq + from_right(aq)) + (PD + cPD), kN = T(4) * t + (PD + PDW);
+        T kE = T(4) * (aq + from_right(aq)) + (PD + cPD), kN = T(4) * t + (PD + PDW);
+        pause_issue<kPause>(kE);
+        pause_issue<kPause>(kN);
         const T gE = from_right(uS) - uS, gN = uC - uS;
-        const T gNE = from_right(uC) - uS, gNW = from_left(uC) - uS;
+        T gNE = from_right(uC) - uS, gNW = from_left(uC) - uS;
+        pause_issue<kPause>(gNE);
+        pause_issue<kPause>(gNW);
         T fE = kE * gE, fN = kN * gN;
         T d1 = PD * gNE, d2 = PDW * gNW;
 
         T PA = T(0);
         if constexpr (!kDiff) {
-          const T tA = aAS + aAC;
+          T tA = aAS + aAC;
+          pause_issue<kPause>(tA);
           PA = tA + from_right(tA);
+          pause_issue<kPause>(PA);
           const T PAW = from_left(PA);
           T fEA = (T(4) * (aAS + from_right(aAS)) + (PA + cPA)) * (pSE - pS);
           T fNA = (T(4) * tA + (PA + PAW)) * (pC - pS);
+          pause_issue<kPause>(fEA);
+          pause_issue<kPause>(fNA);
           T d1A = PA * (pCE - pS);
           T d2A = PAW * (pCW - pS);
           if constexpr (kAT == kAtFullShells) {
@@ -456,6 +480,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
             // neighbours' values
             auto inv = [&](T gx, T gy) {
               T g2 = gx * gx + gy * gy;
+              pause_issue<kPause>(g2);
               return g2 > c.at_eps ? M::rsq(g2) : T(0);
             };
             const T k1 = T(35.0 / 48.0), k2 = T(1.0 / 48.0), k3 = T(1.0 / 6.0);
@@ -502,12 +527,15 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
             fN = fNA + kN * gN;
             d1 = d1A + PD * gNE;
             d2 = d2A + PDW * gNW;
+            pause_issue<kPause>(fE);
+            pause_issue<kPause>(d2);
           }
         }
 
         if constexpr (P >= 4) {
           T div = c.cD1 * ((fE - from_left(fE)) + (fN - cN)) +
                   c.cD2 * ((d1 - from_left(c1)) + (d2 - from_right(c2)));
+          pause_issue<kPause>(div);
           // the held psi has no anti-trapping current and no source
           T rU = (kDiff ? div : div + sq2 * aAS) * M::rcp(T(1) + c.k - c.omk * fS);
           store_row(a.U_out + (size_t)q * (size_t)nx, nx, x, out_lane, uS + c.dt * rU);

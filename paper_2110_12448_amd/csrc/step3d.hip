@@ -57,12 +57,16 @@ __device__ __forceinline__ T aniso3(T gx, T gy, T gz, const Rot3<T> &R, const Co
                                     T eps) {
   // (below the guard r2 may be inf: the selects drop what it feeds)
   T g2 = gx * gx + gy * gy + gz * gz;
+  pause_issue(g2);
   T r2 = Math<T>::rcp(g2);
   T c0 = R.m[0] * gx + R.m[3] * gy + R.m[6] * gz;
   T c1 = R.m[1] * gx + R.m[4] * gy + R.m[7] * gz;
   T c2 = R.m[2] * gx + R.m[5] * gy + R.m[8] * gz;
+  pause_issue(c0);
+  pause_issue(c2);
   T q0 = c0 * c0, q1 = c1 * c1, q2 = c2 * c2;
   T s4 = (q0 * q0 + q1 * q1 + q2 * q2) * (r2 * r2);
+  pause_issue(s4);
   T a = c.an0 + c.an4 * s4;
   if constexpr (comp < 0) {
     return g2 > eps ? a : T(1);
@@ -70,10 +74,12 @@ __device__ __forceinline__ T aniso3(T gx, T gy, T gz, const Rot3<T> &R, const Co
     T t = c.an16 * a;
     T base = a * a - t * s4;
     T tr = t * r2;
+    pause_issue(base);
     T j0 = c0 * (base + tr * q0);
     T j1 = c1 * (base + tr * q1);
     T j2 = c2 * (base + tr * q2);
     T j = R.m[3 * comp + 0] * j0 + R.m[3 * comp + 1] * j1 + R.m[3 * comp + 2] * j2;
+    pause_issue(j);
     T plain = comp == 0 ? gx : (comp == 1 ? gy : gz);
     return g2 > eps ? j : plain;
   }
@@ -398,14 +404,17 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       auto opp = [&](int dx, int dy, int dz) -> T {  // difference of an opposite pair
         return Pn[nb(dx, dy, dz)] - Pn[nb(-dx, -dy, -dz)];
       };
-      const T s1 = ((dif(-1, 0, 0) + dif(1, 0, 0)) + (dif(0, -1, 0) + dif(0, 1, 0))) +
+      T s1 = ((dif(-1, 0, 0) + dif(1, 0, 0)) + (dif(0, -1, 0) + dif(0, 1, 0))) +
                    (dif(0, 0, -1) + dif(0, 0, 1));
-      const T s2 = (((dif(-1, -1, 0) + dif(1, 1, 0)) + (dif(-1, 1, 0) + dif(1, -1, 0))) +
+      pause_issue(s1);
+      T s2 = (((dif(-1, -1, 0) + dif(1, 1, 0)) + (dif(-1, 1, 0) + dif(1, -1, 0))) +
                     ((dif(0, -1, -1) + dif(0, 1, 1)) + (dif(0, -1, 1) + dif(0, 1, -1)))) +
                    ((dif(-1, 0, -1) + dif(1, 0, 1)) + (dif(-1, 0, 1) + dif(1, 0, -1)));
+      pause_issue(s2);
       const T e1 = opp(1, 1, 0), e2 = opp(1, -1, 0), e3 = opp(0, 1, 1), e4 = opp(0, 1, -1);
       const T e5 = opp(1, 0, 1), e6 = opp(1, 0, -1);
-      const T g2 = e1 * e1 + e2 * e2 + e3 * e3 + e4 * e4 + e5 * e5 + e6 * e6;
+      T g2 = e1 * e1 + e2 * e2 + e3 * e3 + e4 * e4 + e5 * e5 + e6 * e6;
+      pause_issue(g2);
       const Rot3<T> R = rot_of(gC);
       // central differences (2h g at the centre); the face gradients below
       // are 4h g: the normal difference times 4 and, for each tangential
@@ -425,6 +434,7 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
         lap += c.rA3 * s3;
         grd += c.rB3 * (e7 * e7 + e8 * e8 + e9 * e9 + e10 * e10);
       }
+      pause_issue(grd);
       const T lg = lap + fC * grd;
       T ac = aniso3<T, -1>(cx, cy, cz, R, c, c.ac_eps);
       // x face east of the cell (the right lane's differences by DPP)
@@ -450,6 +460,8 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
                            T(4) * (p0 - Pn[nb(0, 0, -1)]), Rd, c, c.f3_eps);
         if (zr == 0) FZ[lx] = fzd;
       }
+      // (FP64 likewise here, -1.5%; FP32 ran 0.7% slower)
+      if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
       __syncthreads();
       const T FzD = FZ[zr * GL + lx];
       const T ac2 = ac * ac;
@@ -462,7 +474,8 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
         F2 = uC + zl;
       }
       const T omp = T(1) - fC * fC;
-      const T rhs = (ac2 * lg + T(0.25) * flux) + c.rK * (fC - (c.lambda * omp) * F2);
+      T rhs = (ac2 * lg + T(0.25) * flux) + c.rK * (fC - (c.lambda * omp) * F2);
+      pause_issue(rhs);
       const T rate = rhs * M::rcp(F1 * ac2);
       T aA = (T(1) + c.omk * uC) * omp * rate * T(0.5);
       if (a.bcx == PF_BC_NOFLUX) {  // mirrored columns take their image's value
@@ -540,16 +553,21 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       const T a0m = rd(AL, 0, -1, 0), a0p = rd(AL, 0, 1, 0);
       const T a1m = rd(AL, 1, -1, 0), a1p = rd(AL, 1, 1, 0);
       o.Py1 = T(4) * a10 + ((rd(AL, 1, 0, -1) + rd(AL, 1, 0, 1)) + (a1m + a1p));
+      pause_issue(o.Py1);
       o.N = Pyq + o.Py1;
       // xy plaquettes {x, x+1} x {q, q+1} at z-1, z, z+1
-      const T cm = a0m + a1m, c0 = a00 + a10, cp = a0p + a1p;
+      T cm = a0m + a1m, c0 = a00 + a10, cp = a0p + a1p;
+      pause_issue(c0);
       const T Xm = cm + from_right(cm), X0 = c0 + from_right(c0), Xp = cp + from_right(cp);
       o.NE = T(6) * X0 + (Xm + Xp);
+      pause_issue(o.NE);
       o.NW = from_left(o.NE);
       // yz plaquettes {q, q+1} x {z, z+1} (NU) and {z-1, z} (ND) at x-1, x, x+1
       const T S = c0 + cp, Sd = cm + c0;
       o.NU = T(6) * S + (from_left(S) + from_right(S));
+      pause_issue(o.NU);
       o.ND = T(6) * Sd + (from_left(Sd) + from_right(Sd));
+      pause_issue(o.ND);
       if constexpr (kShell3) {
         // the cube {x, x+1} x {q, q+1} x {z, z+1} is two stacked plaquettes
         o.Tpp = X0 + Xp;
@@ -564,13 +582,17 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
         const T yy = am0 + a10;
         const T Px = T(4) * a00 + (yy + (a0m + a0p));
         o.E = Px + from_right(Px);
+        pause_issue(o.E);
         const T Pz0 = T(4) * a00 + ((rd(AL, 0, 0, -1) + rd(AL, 0, 0, 1)) + yy);
         const T Pz1 = T(4) * a0p + ((rd(AL, 0, 1, -1) + rd(AL, 0, 1, 1)) + (am1 + a1p));
         o.Up = Pz0 + Pz1;
+        pause_issue(o.Up);
         // xz plaquettes {x, x+1} x {z, z+1} at q-1, q, q+1
-        const T ym = am0 + am1, y0s = a00 + a0p, yp = a10 + a1p;
+        T ym = am0 + am1, y0s = a00 + a0p, yp = a10 + a1p;
+        pause_issue(y0s);
         const T Ym = ym + from_right(ym), Y0 = y0s + from_right(y0s), Yp = yp + from_right(yp);
         o.EU = T(6) * Y0 + (Ym + Yp);
+        pause_issue(o.EU);
         o.WU = from_left(o.EU);
       } else {
         o.E = o.Up = o.EU = o.WU = T(0);
@@ -616,6 +638,10 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       if constexpr (!kFull) PyD = py_here(kAD);
       bD = abars(kAD, PyD);
     }
+    // alpha_D's averages are finished before the barrier: the scheduler sank
+    // part of them behind it, ahead of the alpha_A reads that everything after
+    // the barrier waits on (256^3 1149 -> 1125 us for 4 steps)
+    __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
 
     if constexpr (P >= 3) {
@@ -626,10 +652,13 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
       PyD = bD.Py1;
       PyA = bA.Py1;
       // link values: D~ abar_D dU + abar_A dpsi (D~ is inside alpha_D)
-      const T fN_ = bD.N * dU.N + bA.N * dP.N;
-      const T fNE = bD.NE * dU.NE + bA.NE * dP.NE;
+      T fN_ = bD.N * dU.N + bA.N * dP.N;
+      pause_issue(fN_);
+      T fNE = bD.NE * dU.NE + bA.NE * dP.NE;
+      pause_issue(fNE);
       const T fNW = bD.NW * dU.NW + bA.NW * dP.NW;
-      const T fNU = bD.NU * dU.NU + bA.NU * dP.NU;
+      T fNU = bD.NU * dU.NU + bA.NU * dP.NU;
+      pause_issue(fNU);
       const T fND = bD.ND * dU.ND + bA.ND * dP.ND;
       // <111> links towards +y; the wave above takes (-1,+1,+1) of lane x+1 and
       // (+1,+1,+1) of lane x-1 as its south-down links, the wave below the
@@ -645,9 +674,11 @@ __device__ __forceinline__ bool step3d_tile(const Step3DArgs<T> &a, int strip, i
         dn111 = from_right(fmm) + from_left(fpm);
       }
       if constexpr (kFull) {
-        const T fE = bD.E * dU.E + bA.E * dP.E;
+        T fE = bD.E * dU.E + bA.E * dP.E;
+        pause_issue(fE);
         const T fUp = bD.Up * dU.Up + bA.Up * dP.Up;
-        const T fEU = bD.EU * dU.EU + bA.EU * dP.EU;
+        T fEU = bD.EU * dU.EU + bA.EU * dP.EU;
+        pause_issue(fEU);
         const T fWU = bD.WU * dU.WU + bA.WU * dP.WU;
         // links the waves above and below take with the opposite sign
         const int par = (q & 1) * 2 * NW * GL + zr * GL + lx;
