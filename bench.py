@@ -35,30 +35,30 @@ PEAK_FP32_TFLOPS = 157.3       # MI355X FP32 vector (published; counts packed FP
 PEAK_FP32_NONPACKED_TFLOPS = 78.6  # the same vector units issuing one FP32 FMA per lane
 # FP32 operations per cell-update of the 2D step as written in step2d.hip
 # (FMA = 2, each transcendental = 1; index math, selects and cross-lane moves
-# not counted): tanh 6, y-face flux 30, psi rate 112 (L 10, G 9, centre a_s
-# 15, x-face flux 29, remainder 6, thermal 6, bulk, rate and alpha_A 20,
-# update 2, the rest 15), U update 61 (links of D 22 and A 18, combined 4,
-# sums, rate and update 17).
-ALG_FLOPS_2D = 209
+# not counted): phi 6, y-face flux 30, psi rate 96 (row sums 12, L and G 11,
+# centre a_s 15, x-face flux 30, flux sum 3, thermal 5, bulk, rate, alpha_A and
+# update 20), U update 57 (alphas 24, differences 8, products 12, sums, rate
+# and update 13).
+ALG_FLOPS_2D = 189
 # compulsory bytes per cell-update: read psi, U; write psi, U (FP32)
 ALG_BYTES_2D_F32 = 16
 # FP32 operations per cell-update of the 3D step as written in step3d.hip
-# (same counting rules): psi rate 343 (phi 6, L 37, G 30, centre a_s 39, three
-# face fluxes 186 (the z face below is the wave below's z face above),
-# remainder 17, thermal and rate 28), U update 187 (the alpha sums of the 9
-# links a cell owns 2 x 57, their differences 18 and products 27, the
-# exchange, sums and update 26, alpha_D 2).
-ALG_FLOPS_3D = 530
-# with the <111> shell (S-bar_{4,4,1}): + 32 for its Laplacian and gradient
-# square terms, + 37 for its 4 owned divergence links (cube sums from the
+# (same counting rules): psi rate 306 (phi 6, L 37, G 30, centre a_s 28, three
+# face fluxes 172 (the z face below is the wave below's z face above), flux sum
+# 6, thermal, rate, alpha_A and update 27), U update 172 (the alpha sums of the
+# 9 links a cell owns 2 x 46, their differences 18 and products 27, the
+# exchange, sums and update 33, alpha_D 2).
+ALG_FLOPS_3D = 478
+# with the <111> shell (S-bar_{4,4,1}): + 30 for its Laplacian and gradient
+# square terms, + 31 for its 4 owned divergence links (cube sums from the
 # plaquette sums, differences, products, exchange)
-ALG_FLOPS_3D_441 = 599
+ALG_FLOPS_3D_441 = 539
 # read psi, U, the int8 grain; write psi, U
 ALG_BYTES_3D_F32 = 17
 # FP32 operations per cell-update of the 2D step under the three schemes of
 # Table 1 (same counting rules; the full current adds three App. B gradients,
 # the two-point faces replace the shell divergences)
-SCHEME_FLOPS_2D = {"S10": 199, "S21": 295, "Sbar21": 209}
+SCHEME_FLOPS_2D = {"S10": 174, "S21": 275, "Sbar21": 189}
 # Table 1: wall time of the whole isothermal run on a Tesla P100 (context)
 PAPER_TABLE1_S = {"S10": 1359.0, "S21": 4612.0, "Sbar21": 3883.0}
 
@@ -185,7 +185,7 @@ def bench_batched(args):
            "default_segment_value": cells * steps / t_default,
            "one_at_a_time_f32": cells * solo_steps / t32,
            "one_at_a_time_f64": cells * (solo_steps // 2) / t64}
-    # the batched step kernel is the same 2D step body: 209 flops and 16 B of
+    # the batched step kernel is the same 2D step body: 189 flops and 16 B of
     # algorithmic traffic per cell-update
     tfl = ALG_FLOPS_2D * batched / 1e12
     gbs = ALG_BYTES_2D_F32 * batched / 1e9
