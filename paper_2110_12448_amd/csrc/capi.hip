@@ -355,6 +355,12 @@ Coef<T> coef_of(const pf_solver *s) {
     c.an1 = (T)(1.0 + p.eps4);
     c.an2 = (T)(2.0 * p.eps4);
     c.an8 = (T)(8.0 * p.eps4);
+    c.rC1 = (T)(s->w[0] / h2);
+    c.rC2 = (T)(s->w[1] / (2.0 * h2));
+    c.rG1 = (T)(s->w[0] / (4.0 * h2));
+    c.rG2 = (T)(s->w[1] / (8.0 * h2));
+    c.rStd = (T)(1.0 / h2);
+    c.inv_lT = (T)(p.lT > 0.0 ? 1.0 / p.lT : 0.0);
   } else {
     // D_{1,0,0} = sum abar dbeta / h^2; D_{0,1,0}, D_{0,0,1} = / (4h^2); the
     // kernel's averages are 16, 32 and 8 times abar
@@ -387,7 +393,8 @@ int upload(pf_solver *s, const pf_init *init) {
     PF_HIP(hipMemcpy(field<T>(s, k == 0 ? s->L.psi[0] : s->L.U[0]), tmp, n * sizeof(T),
                      hipMemcpyHostToDevice));
   }
-  // rotation table: 2D (cos, sin of twice the angle) per grain, 3D all 9
+  // rotation table: 2D (cos, sin of twice the angle) per grain, then (r00, r01,
+  // r10, r11) per grain; 3D all 9
   const int ng = s->p.n_grains;
   std::vector<T> rt((size_t)ng * 9, (T)0);
   for (int g = 0; g < ng; ++g) {
@@ -397,6 +404,7 @@ int upload(pf_solver *s, const pf_init *init) {
       double_angle(R, &c2, &s2);
       rt[2 * g + 0] = (T)c2;
       rt[2 * g + 1] = (T)s2;
+      for (int i = 0; i < 4; ++i) rt[2 * ng + 4 * g + i] = (T)R[i < 2 ? i : i + 1];
     } else {
       for (int i = 0; i < 9; ++i) rt[9 * g + i] = (T)R[i];
     }
@@ -423,6 +431,7 @@ Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, bool share, int min_seg = 1, int s
   a.grain = p.n_grains > 1 ? grain_buf(s, s->cur) : nullptr;
   a.grain_out = p.dynamic_grains ? grain_buf(s, 1 - s->cur) : nullptr;
   a.rot = field<T>(s, s->L.rot);
+  a.axes = a.rot + 2 * std::max(p.n_grains, 1);
   double c2, s2;
   double_angle(s->rot.data(), &c2, &s2);
   a.c2 = (T)c2; a.s2 = (T)s2;

@@ -17,6 +17,14 @@ template <typename T> struct Math;
 template <> struct Math<float> {
   static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
   static __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
+  // tanh(x) = sign(x) (1 - e) / (1 + e), e = exp(-2|x|), with the hardware
+  // base-2 exponential; absolute error a few ulp of 1.
+  static __device__ __forceinline__ float tanh_(float x) {
+    const float m2log2e = -2.8853900817779268f;  // -2 / ln 2
+    float e = __builtin_amdgcn_exp2f(m2log2e * __builtin_fabsf(x));
+    float t = (1.0f - e) * __builtin_amdgcn_rcpf(1.0f + e);
+    return __builtin_copysignf(t, x);
+  }
   // phi = tanh(psi / sqrt2) = sign(psi) (1 - e) / (1 + e), e = exp(-sqrt2
   // |psi|), with the hardware base-2 exponential; absolute error a few ulp of 1.
   static __device__ __forceinline__ float phi(float psi) {

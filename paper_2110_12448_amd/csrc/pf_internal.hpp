@@ -62,6 +62,7 @@ struct Coef {
   T rB1, rB2, rB3;  // -sqrt2 h^2 times the shell weights of G over their prefactors
   T rK, h2, omkh2;  // sqrt2 h^2, h^2, (1 - k) h^2
   T hT;             // h / lT, 0 when isothermal
+  T rC1, rC2, rG1, rG2, rStd, inv_lT;  // L, G, 1/h^2 and 1/lT unscaled (2D, FP32 full current)
   T kA, kB, kC;     // cD1/16, cD2/32, cD3/8: shell factors of the link sums (3D)
   T f3_eps;         // 16e-12 h^2: the |g|^2 <= 1e-12 guard for 4h g (face gradients, 3D)
 };
@@ -73,6 +74,7 @@ struct Step2DArgs {
   const int8_t *grain;   // multi-grain only
   int8_t *grain_out;     // dynamic grains only: grain map of the next level
   const T *rot;          // multi-grain only: (c2, s2) per grain
+  const T *axes;         // (r00, r01, r10, r11) per grain (FP32 full current on shells)
   T c2, s2;              // single grain: cos and sin of twice its angle
   int nx, ny, bcx, bcy;
   int wout, nstrips, nsegs, segbase, segrem;

@@ -103,6 +103,44 @@ __device__ __forceinline__ T aniso_flux(T gx, T gy, T g2eps, const Rot2<T> &R,
   return comp == 0 ? a * (a * gx + ath * gy) : a * (a * gy - ath * gx);
 }
 
+// The same in the crystal's own axes, for the FP32 full current on shells.  That
+// current divides by App. B's |grad psi|, and where the gradient nearly vanishes
+// (the grooves between fingers) a last-bit change of psi turns its links: after
+// 20 steps two orders of rounding differ there by up to 1e-4 of |U|, each as far
+// from FP64 as the other.  So that this variant's results stay what they have
+// been, it keeps its order of operations (kAxes below).
+template <typename T>
+struct Axes2 {
+  T r00, r01, r10, r11;  // crystal -> lab
+};
+
+template <typename T>
+__device__ __forceinline__ T aniso_a_axes(T gx, T gy, T g2eps, const Axes2<T> &R,
+                                          const Coef<T> &c) {
+  T g2 = gx * gx + gy * gy;
+  T r2 = Math<T>::rcp(g2 > g2eps ? g2 : g2eps);
+  T cx = R.r00 * gx + R.r10 * gy;
+  T cy = R.r01 * gx + R.r11 * gy;
+  T w = cx * cy * r2;
+  T a = c.an1 - c.an8 * w * w;
+  return g2 > g2eps ? a : T(1);
+}
+
+template <typename T, int comp>
+__device__ __forceinline__ T aniso_flux_axes(T gx, T gy, T g2eps, const Axes2<T> &R,
+                                             const Coef<T> &c) {
+  T g2 = gx * gx + gy * gy;
+  T r2 = Math<T>::rcp(g2 > g2eps ? g2 : g2eps);
+  T cx = R.r00 * gx + R.r10 * gy;
+  T cy = R.r01 * gx + R.r11 * gy;
+  T w = cx * cy * r2;
+  T a = c.an1 - c.an8 * w * w;
+  T ath = c.an16 * w * ((cx * cx - cy * cy) * r2);  // -da/dtheta
+  T j = comp == 0 ? a * (a * gx + ath * gy) : a * (a * gy - ath * gx);
+  T plain = comp == 0 ? gx : gy;
+  return g2 > g2eps ? j : plain;
+}
+
 // Logical blocks -> hardware blocks so that each of the 8 XCDs (which take
 // consecutive hardware blocks round-robin) runs a contiguous range of strips
 // and shares their halo rows in its own L2.
@@ -145,6 +183,7 @@ template <typename T, bool kFrozen, bool kReduce, bool kMulti, int kAT, bool kRo
 __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb) {
   constexpr bool kTwoPoint = kAT == kAtFullTwoPoint || kAT == kAtApproxTwoPoint;
   constexpr bool kDiff = kAT == kAtDiffusionOnly;
+  constexpr bool kAxes = kAT == kAtFullShells && sizeof(T) == 4;
   using M = Math<T>;
   const Coef<T> &c = a.c;
   const int lane = threadIdx.x & 63;
@@ -178,7 +217,9 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     const int ye = y0 + a.segbase + (segi < a.segrem ? 1 : 0);
     const int pend = a.frame ? a.frame_in->pending : 0;
     const long long shift = a.frame ? a.frame_in->base + pend : 0;
-    T offT = T(0);  // zeta / lT of row 0
+    T off = T(0), offT = T(0);  // zeta and zeta / lT of row 0
+    if (kFrozen && kAxes)
+      off = (T)((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd));
     if (kFrozen)
       offT = (T)(((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd)) * a.inv_lTd);
     const double ythr = (double)a.shift_row * a.hd;
@@ -217,6 +258,16 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         return Rot2<T>{q[0], q[1]};
       }
       return R0;
+    };
+    auto axes_of = [&](int g) -> Axes2<T> {
+      const T *q = a.axes + 4 * (kMulti ? g : 0);
+      return Axes2<T>{q[0], q[1], q[2], q[3]};
+    };
+    auto phi_of = [&](T p) -> T {
+      if constexpr (kAxes)
+        return M::tanh_(p * T(0.70710678118654752));
+      else
+        return M::phi(p);
     };
 
     // register window: S = row r-2, C = row r-1, N = row r (newest)
@@ -299,7 +350,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
           dN = pN - pC;
         }
       }
-      if (P != 9) fN = M::phi(pN);  // phase 9's row r is past every use of phi
+      if (P != 9) fN = phi_of(pN);  // phase 9's row r is past every use of phi
       if constexpr (P == 0) return;
       if constexpr (kAT == kAtFullShells && P >= 2) {
         pCE2 = from_right(pCE);
@@ -310,7 +361,9 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // fluxes are h J (gradients passed as h g)
       T FyN = T(0);
       if constexpr (!kDiff && P < 8)
-        FyN = aniso_flux<T, 1, kPause>(T(0.25) * (exN + exC), dN, c.at_eps, rot_of(gC), c);
+        FyN = kAxes ? aniso_flux_axes<T, 1>(T(0.25) * (pNE + pCE - pNW - pCW), dN, c.at_eps,
+                                            axes_of(gC), c)
+                    : aniso_flux<T, 1, kPause>(T(0.25) * (exN + exC), dN, c.at_eps, rot_of(gC), c);
       // dynamic grains: the grain of row m at the next level (a liquid cell,
       // psi < 0, with a solid face neighbour takes the grain of the solid
       // neighbour with the largest psi, first of -x, +x, -y, +y on ties)
@@ -352,36 +405,63 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         // ---------------- psi rate at row m (window rows S, C, N = m-1, m, m+1)
         const int m = r - 1;
         grain_next(m);
-        const Rot2<T> R = rot_of(gC);
-        const T dd = dN - dNp;  // (pN - pC) + (pS - pC)
-        const T s10 = sxC + dd;
-        T s11 = (sxN + sxS) + T(2) * dd;
-        pause_issue<kPause>(s11);
-        T ey = pN - pS;
-        pause_issue<kPause>(ey);
-        const T e1 = pNE - pSW, e2 = pSE - pNW;
-        const T ac = aniso_a<T, kPause>(exC, ey, c.ac_eps, R, c);  // (exC, ey) = 2h g
-        const T FxE = aniso_flux<T, 0, kPause>(pCE - pC, T(0.25) * (ey + from_right(ey)), c.at_eps, R, c);
-        const T FxW = from_left(FxE);
-        const T ac2 = ac * ac;
-        // h^2 times the right-hand side: ac^2 (L - sqrt2 phi G) with the
-        // standard Laplacian of the eps4 remainder (s10) taken off L, the
-        // face fluxes, and the bulk terms
-        T lg = (c.rA1 * s10 + c.rA2 * s11) +
-                     fC * (c.rB1 * (exC * exC + ey * ey) + c.rB2 * (e1 * e1 + e2 * e2));
-        pause_issue<kPause>(lg);
-        const T flux = (FxE - FxW) + (FyN - FyS);
-        T F1 = c.h2, F2 = uC;  // F1 times h^2
-        if (kFrozen) {
-          const T zl = (T)(P >= 5 ? m : ghost_near(m, ny, a.bcy)) * c.hT + offT;  // zeta / lT
-          F1 = c.h2 - c.omkh2 * zl;
-          F2 = uC + zl;
+        T omp, rate;
+        if constexpr (kAxes) {
+          const Axes2<T> R = axes_of(gC);
+          T dE = pCE - pC, dW = pCW - pC, dS = pS - pC;
+          T s10 = dE + dW + dN + dS;
+          T s11 = (pNE - pC) + (pNW - pC) + (pSE - pC) + (pSW - pC);
+          T L = c.rC1 * s10 + c.rC2 * s11;
+          T ey = pN - pS;
+          T e1 = pNE - pSW, e2 = pSE - pNW;
+          T G = c.rG1 * (exC * exC + ey * ey) + c.rG2 * (e1 * e1 + e2 * e2);
+          T ac = aniso_a_axes(exC, ey, c.ac_eps, R, c);  // (exC, ey) = 2h g
+          T FxE = aniso_flux_axes<T, 0>(dE, T(0.25) * (pN + pNE - pS - pSE), c.at_eps, R, c);
+          T FxW = from_left(FxE);
+          T ac2 = ac * ac;
+          T Nn = (FxE - FxW + FyN - FyS - ac2 * s10) * c.rStd;
+          T F1 = T(1), F2 = uC;
+          if (kFrozen) {
+            T zeta = (T)(P >= 5 ? m : ghost_near(m, ny, a.bcy)) * c.h + off;
+            F1 = T(1) - c.omk * zeta * c.inv_lT;
+            F2 = uC + zeta * c.inv_lT;
+          }
+          T ph = fC;
+          omp = T(1) - ph * ph;
+          T rhs = ac2 * (L - sq2 * ph * G) + Nn + sq2 * (ph - c.lambda * omp * F2);
+          rate = rhs * M::rcp(F1 * ac2);
+        } else {
+          const Rot2<T> R = rot_of(gC);
+          const T dd = dN - dNp;  // (pN - pC) + (pS - pC)
+          const T s10 = sxC + dd;
+          T s11 = (sxN + sxS) + T(2) * dd;
+          pause_issue<kPause>(s11);
+          T ey = pN - pS;
+          pause_issue<kPause>(ey);
+          const T e1 = pNE - pSW, e2 = pSE - pNW;
+          const T ac = aniso_a<T, kPause>(exC, ey, c.ac_eps, R, c);  // (exC, ey) = 2h g
+          const T FxE = aniso_flux<T, 0, kPause>(pCE - pC, T(0.25) * (ey + from_right(ey)), c.at_eps, R, c);
+          const T FxW = from_left(FxE);
+          const T ac2 = ac * ac;
+          // h^2 times the right-hand side: ac^2 (L - sqrt2 phi G) with the
+          // standard Laplacian of the eps4 remainder (s10) taken off L, the
+          // face fluxes, and the bulk terms
+          T lg = (c.rA1 * s10 + c.rA2 * s11) +
+                       fC * (c.rB1 * (exC * exC + ey * ey) + c.rB2 * (e1 * e1 + e2 * e2));
+          pause_issue<kPause>(lg);
+          const T flux = (FxE - FxW) + (FyN - FyS);
+          T F1 = c.h2, F2 = uC;  // F1 times h^2
+          if (kFrozen) {
+            const T zl = (T)(P >= 5 ? m : ghost_near(m, ny, a.bcy)) * c.hT + offT;  // zeta / lT
+            F1 = c.h2 - c.omkh2 * zl;
+            F2 = uC + zl;
+          }
+          omp = T(1) - fC * fC;
+          pause_issue<kPause>(omp);
+          T rhs = (ac2 * lg + flux) + c.rK * (fC - (c.lambda * omp) * F2);
+          pause_issue<kPause>(rhs);
+          rate = rhs * M::rcp(F1 * ac2);
         }
-        T omp = T(1) - fC * fC;
-        pause_issue<kPause>(omp);
-        T rhs = (ac2 * lg + flux) + c.rK * (fC - (c.lambda * omp) * F2);
-        pause_issue<kPause>(rhs);
-        const T rate = rhs * M::rcp(F1 * ac2);
         T aA = (T(1) + c.omk * uC) * omp * rate * T(0.5);
         if (P == 6 || ((P < 5 || P == 7) && a.bcx == PF_BC_NOFLUX)) {  // mirrored columns copy their image
           T fr = from_right(aA), fl = from_left(aA);
@@ -447,10 +527,12 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         // above and below, 4 abar_N = 4 t + plaquettes right and left
         T t = aq + aq1;
         pause_issue<kPause>(t);
-        T PD = t + from_right(t);
+        T PD = kAxes ? aq + from_right(aq) + aq1 + from_right(aq1) : t + from_right(t);
         pause_issue<kPause>(PD);
         const T PDW = from_left(PD);
-        T kE = T(4) * (aq + from_right(aq)) + (PD + cPD), kN = T(4) * t + (PD + PDW);
+        T kE = kAxes ? T(4) * (aq + from_right(aq)) + PD + cPD
+                     : T(4) * (aq + from_right(aq)) + (PD + cPD);
+        T kN = kAxes ? T(4) * t + PD + PDW : T(4) * t + (PD + PDW);
         pause_issue<kPause>(kE);
         pause_issue<kPause>(kN);
         const T gE = from_right(uS) - uS, gN = uC - uS;
@@ -464,11 +546,12 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         if constexpr (!kDiff) {
           T tA = aAS + aAC;
           pause_issue<kPause>(tA);
-          PA = tA + from_right(tA);
+          PA = kAxes ? aAS + from_right(aAS) + aAC + from_right(aAC) : tA + from_right(tA);
           pause_issue<kPause>(PA);
           const T PAW = from_left(PA);
-          T fEA = (T(4) * (aAS + from_right(aAS)) + (PA + cPA)) * (pSE - pS);
-          T fNA = (T(4) * tA + (PA + PAW)) * (pC - pS);
+          T fEA = (kAxes ? T(4) * (aAS + from_right(aAS)) + PA + cPA
+                         : T(4) * (aAS + from_right(aAS)) + (PA + cPA)) * (pSE - pS);
+          T fNA = (kAxes ? T(4) * tA + PA + PAW : T(4) * tA + (PA + PAW)) * (pC - pS);
           pause_issue<kPause>(fEA);
           pause_issue<kPause>(fNA);
           T d1A = PA * (pCE - pS);
@@ -533,8 +616,10 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
         }
 
         if constexpr (P >= 4) {
-          T div = c.cD1 * ((fE - from_left(fE)) + (fN - cN)) +
-                  c.cD2 * ((d1 - from_left(c1)) + (d2 - from_right(c2)));
+          T div = kAxes ? c.cD1 * (fE - from_left(fE) + fN - cN) +
+                              c.cD2 * (d1 + d2 - from_left(c1) - from_right(c2))
+                        : c.cD1 * ((fE - from_left(fE)) + (fN - cN)) +
+                              c.cD2 * ((d1 - from_left(c1)) + (d2 - from_right(c2)));
           pause_issue<kPause>(div);
           // the held psi has no anti-trapping current and no source
           T rU = (kDiff ? div : div + sq2 * aAS) * M::rcp(T(1) + c.k - c.omk * fS);
@@ -616,8 +701,8 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
       // the pipeline computed from the same loads
       const int ms = a.shift_row - 1;
       if (ms >= y0 && ms < ye && ms <= ny - 2) {
-        const T f0 = M::phi(a.psi_in[(size_t)row_of(ms) * nx + gx]);
-        const T f1 = M::phi(a.psi_in[(size_t)row_of(ms + 1) * nx + gx]);
+        const T f0 = phi_of(a.psi_in[(size_t)row_of(ms) * nx + gx]);
+        const T f1 = phi_of(a.psi_in[(size_t)row_of(ms + 1) * nx + gx]);
         if (out_lane && f0 >= T(0) && f1 < T(0))
           over |= crossing_reaches(f0, f1, ms, a.shift_row, ythr, a.hd);
       }
