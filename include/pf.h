@@ -311,9 +311,9 @@ int pf_batch_use_graph(pf_batch *b, int32_t steps_per_graph);
 /* Batch autotuner: time the batched step for one segment length shared by
  * every member (4..32 rows) against the one in use (initially each member's
  * own segment length, at least 8 rows; for a member whose geometry asks for
- * waves per SIMD, the longest segment that gives alone) over
- * steps_per_trial steps on scratch copies of all
- * member workspaces, with the same passes and margins as pf_autotune,
+ * waves per SIMD, the longest segment that gives alone, at least 8, 20 or 32
+ * rows by the size of the whole batch) over steps_per_trial steps on scratch
+ * copies of all member workspaces, with the same passes and margins as pf_autotune,
  * then rebuild the batch with the choice (kept until the batch is destroyed;
  * it overrides the members' own pf_tune settings inside the batch only).  The
  * members do not advance.  Synchronises.  *seg (may be NULL) receives the

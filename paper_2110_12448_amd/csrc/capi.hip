@@ -84,8 +84,20 @@ int default_seg2d(int nx, int ny, int precision, int ncu) {
   return -std::min(64, std::max(1, (int)std::lround(k)));
 }
 // Batched members keep segments of at least 8 rows: the batch fills the chip
-// by itself.
+// by itself.  A segment repeats about 3 rows of work, so members that nobody
+// tuned take 20 rows from 60 strip rows per SIMD in the whole batch on, and 32
+// from 160 on; below 60 that would leave SIMDs idle.  us a step with 8 / 20 / 32
+// rows, FP32 (FP64), sides and strip rows R per SIMD:
+//    16 of 100-400,  R  20:  12.7 /  17.4 /  19.2  (23.5 / 30.2 / 29.9)
+//    16 of 150-600,  R  43:  21.1 /  22.8 /  24.9  (38.7 / 39.9 / 42.4)
+//     8 of 256-1024, R  62:  27.5 /  27.4 /  31.2  (52.9 / 51.1 / 56.4)
+//    16 of 200-800,  R  75:  29.8 /  27.5 /  31.7  (58.7 / 51.5 / 57.3)
+//    12 of 300-900,  R  78:  31.8 /  32.5 /  31.8  (63.0 / 60.7 / 57.1)
+//    16 of 256-1024, R 122:  44.1 /  41.5 /  45.8  (101.5 / 89.7 / 93.8)
+//    32 of 256-1024, R 242:  80.6 /  75.1 /  76.1  (215.1 / 184.6 / 178.1)
+//    64 of 256-1024, R 483: 179.6 / 154.6 / 146.3  (416.4 / 350.1 / 325.9)
 constexpr int kMinSegBatch2D = 8;
+int batch_rows2d(double R) { return R < 60.0 ? kMinSegBatch2D : R < 160.0 ? 20 : 32; }
 constexpr size_t kMaxLds3DBytes = 163840;  // LDS one gfx950 workgroup may allocate
 constexpr size_t kMaxLds3D = kMaxLds3DBytes;
 // Default 3D geometry.  z rows per wide workgroup: 14, 6 or 2 in FP32 (16, 8
@@ -600,11 +612,15 @@ int batch_build(pf_batch *b) {
   const int n = (int)b->s.size();
   std::vector<BatchSolve2D<T>> tab(n);
   std::vector<int2> list;
+  double R = 0.0;  // strip rows per SIMD
+  for (const pf_solver *s : b->s)
+    R += (double)((s->p.nx + 59) / 60) * s->p.ny / (4.0 * std::max(1, s->ncu));
+  const int rows = batch_rows2d(R);
   for (int i = 0; i < n; ++i) {
     pf_solver *s = b->s[i];
     BatchSolve2D<T> &e = tab[i];
     memset(&e, 0, sizeof(e));
-    Geom2D g = fill2d<T>(s, e.a, true, kMinSegBatch2D, b->seg_fixed);
+    Geom2D g = fill2d<T>(s, e.a, true, s->seg > 0 ? kMinSegBatch2D : rows, b->seg_fixed);
     for (int k = 0; k < 2; ++k) {
       e.psi[k] = field<T>(s, s->L.psi[k]);
       e.U[k] = field<T>(s, s->L.U[k]);

@@ -74,3 +74,22 @@ def test_batched_members_bitwise(frame):
     b.close()
     for s in ss:
         s.close()
+
+
+@pytest.mark.parametrize("members,rows", [(4, 1500), (8, 4100), (20, 4200)])
+def test_default_batch_rows_bitwise(members, rows):
+    """Members nobody tuned, at 12, 64 and 164 strip rows per SIMD of 256 CUs:
+    each side of the lines where a batch takes longer segments."""
+    prs = [wl.problem(2, (61 + i % 3, rows + 13 * i), alpha0_deg=11.0, seed=i, seed_radius=5.0)
+           for i in range(members)]
+    prs += [wl.problem(2, (70, 33), alpha0_deg=11.0, seed=3, seed_radius=5.0)]
+    ss = [pfiso.Solver(pr, precision=pfiso.PF_F32) for pr in prs]
+    b = pfiso.Batch(ss, graph_steps=4)
+    b.step(9)
+    for i in (0, 1, members // 2, members - 1, members):
+        psi, U, _ = _run(prs[i], pfiso.PF_F32, -64, 9)
+        _, bU, bpsi, _ = ss[i].read_fields()
+        assert np.array_equal(psi, bpsi) and np.array_equal(U, bU), i
+    b.close()
+    for s in ss:
+        s.close()
