@@ -1,7 +1,7 @@
 // capi.hip -- the C ABI of include/pf.h: parameter validation, workspace
 // layout, state upload/download and the per-step launch sequence.
+#include <float.h>
 #include <math.h>
-#include <cmath>
 #include <string.h>
 
 #include <algorithm>
@@ -52,8 +52,9 @@ namespace {
 constexpr size_t kHostThreads = 8;
 template <typename F>
 void host_parallel(size_t n, size_t grain, F f) {
-  const size_t hw = std::max(1u, std::thread::hardware_concurrency());
-  const size_t k = std::max<size_t>(1, std::min(std::min(kHostThreads, hw), n / grain));
+  size_t k = std::max<size_t>(1, std::min(kHostThreads, n / grain));
+  if (k > 1) k = std::min<size_t>(k, std::max(1u, std::thread::hardware_concurrency()));
+  if (k == 1) return f(0, n);
   auto piece = [&](size_t i) { f(n * i / k, n * (i + 1) / k); };
   std::thread th[kHostThreads];
   size_t started = 0;
@@ -64,7 +65,11 @@ void host_parallel(size_t n, size_t grain, F f) {
   for (size_t i = started; i < k; ++i) piece(i);
   for (size_t i = 0; i < started; ++i) th[i].join();
 }
-constexpr size_t kHostGrain = 1 << 16;  // cells a thread takes at least
+// Cells a thread takes at least: reading back writes fresh pages and evaluates
+// tanh (448^2 404 -> 272 us with 3 threads); creation only converts and checks,
+// where starting threads for less costs more than they save (700^2 with 7
+// threads of 64k cells 640 -> 780 us).
+constexpr size_t kHostGrain = 1 << 16, kHostGrainIn = 1 << 18;
 
 // thin-interface constant a2 = 47/75 (Sec. 2.1): default lambda = D~ / a2
 constexpr double kA2 = 47.0 / 75.0;
@@ -399,7 +404,7 @@ int upload(pf_solver *s, const pf_init *init) {
   T *tmp = buf.get();
   for (int k = 0; k < 2; ++k) {
     const double *src = k == 0 ? init->psi : init->U;
-    host_parallel(n, kHostGrain, [&](size_t b, size_t e) {
+    host_parallel(n, kHostGrainIn, [&](size_t b, size_t e) {
       for (size_t i = b; i < e; ++i) tmp[i] = (T)src[i];
     });
     PF_HIP(hipMemcpy(field<T>(s, k == 0 ? s->L.psi[0] : s->L.U[0]), tmp, n * sizeof(T),
@@ -1006,16 +1011,20 @@ int pf_create(const pf_params *p, const pf_init *init, void *workspace, size_t w
   if (!out) return fail(PF_ERR_ARG, "out is NULL");
   const size_t n = cells(p);
   std::atomic<bool> bad{false};
-  host_parallel(n, kHostGrain, [&](size_t b, size_t e) {
-    bool any = false;
-    for (size_t i = b; i < e; ++i) any |= !isfinite(init->psi[i]) || !isfinite(init->U[i]);
+  host_parallel(n, kHostGrainIn, [&](size_t b, size_t e) {
+    const double *psi = init->psi, *U = init->U;
+    int any = 0;  // no branch on a cell, so the loop vectorises (half the time)
+    for (size_t i = b; i < e; ++i)
+      any |= (int)!(fabs(psi[i]) <= DBL_MAX) | (int)!(fabs(U[i]) <= DBL_MAX);
     if (any) bad.store(true, std::memory_order_relaxed);
   });
   if (bad.load()) return fail(PF_ERR_NONFINITE, "initial psi or U holds NaN or Inf");
   if (init->grain) {
-    host_parallel(n, kHostGrain, [&](size_t b, size_t e) {
-      bool any = false;
-      for (size_t i = b; i < e; ++i) any |= init->grain[i] < 0 || init->grain[i] >= p->n_grains;
+    host_parallel(n, kHostGrainIn, [&](size_t b, size_t e) {
+      const int8_t *g = init->grain;
+      const int ng = p->n_grains;
+      int any = 0;
+      for (size_t i = b; i < e; ++i) any |= (int)(g[i] < 0) | (int)(g[i] >= ng);
       if (any) bad.store(true, std::memory_order_relaxed);
     });
     if (bad.load()) return fail(PF_ERR_ARG, "grain index outside [0, n_grains)");
