@@ -390,6 +390,18 @@ Coef<T> coef_of(const pf_solver *s) {
   return c;
 }
 
+// 2D grains may be turned over (R_zz = -1, a half turn about an in-plane axis):
+// the step kernels take the rotation's angle about z, so such a grain is first
+// turned about the crystal's own x axis, which leaves the cubic form unchanged.
+void upright_2d(std::vector<double> &rot) {
+  for (size_t g = 0; g + 9 <= rot.size(); g += 9)
+    if (rot[g + 8] < 0.0)
+      for (int i = 0; i < 9; i += 3) {
+        rot[g + i + 1] = -rot[g + i + 1];
+        rot[g + i + 2] = -rot[g + i + 2];
+      }
+}
+
 // cos and sin of twice the angle of a rotation about z (row-major 3 x 3)
 void double_angle(const double *R, double *c2, double *s2) {
   *c2 = R[0] * R[4] + R[1] * R[3];
@@ -1048,6 +1060,7 @@ int pf_create(const pf_params *p, const pf_init *init, void *workspace, size_t w
   if (!s) return fail(PF_ERR_OOM, "host allocation failed");
   s->p = *p;
   s->rot.assign(p->grain_rot, p->grain_rot + 9 * p->n_grains);
+  if (p->dim == 2) upright_2d(s->rot);
   s->p.grain_rot = s->rot.data();
   weights_of(p, s->w);
   s->lambda = lambda;
