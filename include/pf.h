@@ -248,7 +248,7 @@ int pf_frame_state(pf_solver *s, int64_t *shift, int32_t *pending);
  * 4..256; in 2D also -k for k = 1..64, asking for k waves per SIMD of the
  * device: each 60-column strip then takes as many segments as give k * 4 *
  * (compute units) waves in all, at most one per row, and the rows are split
- * evenly between them) and z rows per workgroup (3D, 1..14 in FP32, 1..6 in
+ * evenly between them; rows r give ceil(ny / r) segments, none longer) and z rows per workgroup (3D, 1..14 in FP32, 1..6 in
  * FP64, within the LDS of one workgroup; ignored in 2D).  Results do not
  * depend on it (only the work split changes); used by the tile autotuner.
  * PF_ERR_ARG outside these ranges. */
@@ -261,6 +261,11 @@ int pf_tune(pf_solver *s, int32_t rows_per_segment, int32_t z_tile);
  * Either pointer may be NULL.  PF_ERR_ARG for a NULL solver.  (Launch
  * geometry is not part of the paper's method: results never depend on it.) */
 int pf_geometry(pf_solver *s, int32_t *rows_per_segment, int32_t *z_tile);
+
+/* Waves that one pf_step launch runs at the geometry in use: in 2D one per
+ * 60-column strip and segment, in 3D those of every workgroup (launch
+ * geometry: no part of the paper's method).  PF_ERR_ARG for a NULL pointer. */
+int pf_launch_waves(pf_solver *s, int64_t *waves);
 
 /* Tile autotuner: time each candidate launch geometry (2D: 1..32 waves per
  * SIMD, as pf_tune's -k; 3D: rows per segment 8..256 times z rows per workgroup, within the

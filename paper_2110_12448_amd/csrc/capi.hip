@@ -451,12 +451,9 @@ int8_t *grain_buf(pf_solver *s, int k) {
 
 // Argument block of the 2D step of solver s (pointers set per launch).
 template <typename T>
-Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, bool share, int min_seg = 1, int seg_fixed = 0) {
+void fill2d(pf_solver *s, Step2DArgs<T> &a, const Geom2D &g) {
   const pf_params &p = s->p;
   memset(&a, 0, sizeof(a));
-  Geom2D g = seg_fixed > 0   ? geom2d(p.nx, p.ny, seg_fixed, 0, share)
-             : min_seg <= 1 ? geom2d(p.nx, p.ny, s->seg, s->ncu, share)
-                            : geom2d(p.nx, p.ny, std::max(rows2d(s), min_seg), 0, share);
   a.grain = p.n_grains > 1 ? grain_buf(s, s->cur) : nullptr;
   a.grain_out = p.dynamic_grains ? grain_buf(s, 1 - s->cur) : nullptr;
   a.rot = field<T>(s, s->L.rot);
@@ -468,12 +465,11 @@ Geom2D fill2d(pf_solver *s, Step2DArgs<T> &a, bool share, int min_seg = 1, int s
   a.wout = g.wout; a.nstrips = g.nstrips; a.nsegs = g.nsegs;
   a.segbase = g.segbase; a.segrem = g.segrem;
   a.strip_rcp = (unsigned)std::min<unsigned long long>((1ULL << 32) / g.nstrips, 0xffffffffULL);
-  a.shared = g.shared;
+  a.nshared = g.nshared; a.sharedsegs = g.sharedsegs;
   a.c = coef_of<T>(s);
   a.hd = p.h; a.y0 = p.y0; a.Vp = p.Vp; a.dtd = s->dt;
   a.inv_lTd = p.lT > 0.0 ? 1.0 / p.lT : 0.0;
   a.frame = p.frame; a.shift_row = p.shift_row;
-  return g;
 }
 
 template <typename T>
@@ -486,7 +482,8 @@ int step_impl(pf_solver *s, long long nsteps, bool diffusion_only = false) {
   auto frec = [&](int i) { return reinterpret_cast<FrameState *>(s->ws + s->L.frame[i % 3]); };
   if (p.dim == 2) {
     Step2DArgs<T> a;
-    Geom2D g = fill2d<T>(s, a, !diffusion_only);
+    const Geom2D g = geom2d(p.nx, p.ny, s->seg, s->ncu, !diffusion_only);
+    fill2d<T>(s, a, g);
     (void)c;
     const bool two = p.divergence == PF_DIV_TWO_POINT;
     const int at = diffusion_only ? kAtDiffusionOnly
@@ -637,7 +634,10 @@ int batch_build(pf_batch *b) {
     pf_solver *s = b->s[i];
     BatchSolve2D<T> &e = tab[i];
     memset(&e, 0, sizeof(e));
-    Geom2D g = fill2d<T>(s, e.a, true, s->seg > 0 ? kMinSegBatch2D : rows, b->seg_fixed);
+    const int seg = b->seg_fixed > 0 ? b->seg_fixed
+                                     : std::max(rows2d(s), s->seg > 0 ? kMinSegBatch2D : rows);
+    const Geom2D g = geom2d(s->p.nx, s->p.ny, seg, 0, true);
+    fill2d<T>(s, e.a, g);
     for (int k = 0; k < 2; ++k) {
       e.psi[k] = field<T>(s, s->L.psi[k]);
       e.U[k] = field<T>(s, s->L.U[k]);
@@ -1263,6 +1263,19 @@ int pf_tune(pf_solver *s, int32_t rows_per_segment, int32_t z_tile) {
     return fail(PF_ERR_ARG, "z_tile too large for the LDS of one workgroup at this precision");
   s->seg = rows_per_segment;
   if (s->p.dim == 3) s->ztile = z_tile;
+  return PF_OK;
+}
+
+int pf_launch_waves(pf_solver *s, int64_t *waves) {
+  if (!s || !waves) return fail(PF_ERR_ARG, "solver or waves is NULL");
+  const pf_params &p = s->p;
+  if (p.dim == 2) {
+    const Geom2D g = geom2d(p.nx, p.ny, s->seg, s->ncu, true);
+    *waves = (int64_t)g.nstrips * g.nsegs;
+  } else {
+    const Geom3D g = geom3d(p.nx, p.ny, p.nz, s->seg, s->ztile);
+    *waves = (int64_t)g.blocks * (g.threads / 64);
+  }
   return PF_OK;
 }
 

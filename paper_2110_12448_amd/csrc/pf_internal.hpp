@@ -79,7 +79,8 @@ struct Step2DArgs {
   int nx, ny, bcx, bcy;
   int wout, nstrips, nsegs, segbase, segrem;
   unsigned strip_rcp;    // floor(2^32 / nstrips), at most 2^32 - 1
-  int shared;            // waves of a workgroup share a strip and their junctions
+  int nshared;           // workgroups whose waves share a strip and their junctions
+  int sharedsegs;        // segments of each strip they hold, a multiple of 4
   Coef<T> c;
   double hd, y0, Vp, dtd, inv_lTd;
   long long step;
@@ -137,9 +138,12 @@ struct ReduceArgs {
 // Launch geometry of the 2D step: wave64 strips of up to 60 output columns
 // and, per strip, ceil(ny / seg) segments for seg > 0, or for seg = -k as
 // many as give k waves per SIMD over ncu compute units (at most ny); the rows
-// are split evenly (segbase rows each, one more for the first segrem).
+// are split evenly (segbase rows each, one more for the first segrem).  With
+// share and at least 3 rows a segment, the first sharedsegs = nsegs / 4 * 4
+// segments of a strip run as groups of four that share their junctions
+// (nshared workgroups), the others on their own.
 struct Geom2D {
-  int wout, nstrips, nsegs, seg, segbase, segrem, blocks, shared;
+  int wout, nstrips, nsegs, seg, segbase, segrem, blocks, nshared, sharedsegs;
 };
 Geom2D geom2d(int nx, int ny, int seg, int ncu, bool share);
 

@@ -172,13 +172,15 @@ constexpr int kMinWavesBatch2D = sizeof(T) == 4 ? 4 : kMinWaves2D<T, kMulti, kAt
 
 // One logical workgroup `lb` (4 waves) of the step of one solve `a`.
 //
-// Shared segments (a.shared): the 4 waves of a workgroup hold consecutive
-// segments of one strip, and each wave but the top one takes the U rows y0 + 1
-// .. ye (the bottom one y0 too) with alpha_A of rows ye and ye + 1 from the
-// wave above, which leaves them in LDS when it has started; so the psi rate of
-// a junction row is computed once, and a wave above the bottom one starts
-// without the row below its segment.  Otherwise the 4 waves are independent
-// (neighbouring strips), each with its own start and end.
+// Shared segments (the first a.nshared workgroups): the 4 waves of a workgroup
+// hold consecutive segments of one strip, and each wave but the top one takes
+// the U rows y0 + 1 .. ye (the bottom one y0 too) with alpha_A of rows ye and
+// ye + 1 from the wave above, which leaves them in LDS when it has started; so
+// the psi rate of a junction row is computed once, and a wave above the bottom
+// one starts without the row below its segment.  In the workgroups after them
+// (the 1 to 3 segments at the top of each strip that make no group of four, or
+// all segments where they are too short) the 4 waves are independent, of
+// neighbouring strips, each with its own start and end.
 template <typename T, bool kFrozen, bool kReduce, bool kMulti, int kAT, bool kRowTail = true>
 __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb) {
   constexpr bool kTwoPoint = kAT == kAtFullTwoPoint || kAT == kAtApproxTwoPoint;
@@ -189,25 +191,26 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
   const int lane = threadIdx.x & 63;
   // wave-uniform: keeps strip, segment and row counters in scalar registers
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int wave = lb * 4 + wv;
   const int nx = a.nx, ny = a.ny;
 
   bool over_any = false;
 
   __shared__ T xA[4][2][64];  // alpha_A of the first two rows of each wave (shared segments)
-  const bool shared = !kDiff && a.shared;
+  const bool shared = !kDiff && lb < a.nshared;
   const bool first = !shared || wv == 0, last = !shared || wv == 3;
 
-  if (wave < a.nstrips * a.nsegs) {
-    // shared: nsegs is a multiple of 4, so every wave of the workgroup is here
-    // (strip fastest; the quotient by the host's reciprocal, whose estimate
-    // is at most one too small: an integer division costs about 40
-    // instructions before the first load can be issued)
-    const unsigned n = shared ? (unsigned)lb : (unsigned)wave;
+  // group of four segments (shared) or segment above the groups, strip fastest
+  const int item = shared ? lb : (kDiff ? lb : lb - a.nshared) * 4 + wv;
+  const int seg0 = kDiff ? 0 : a.sharedsegs;  // first segment above the groups
+  if (shared || item < a.nstrips * (a.nsegs - seg0)) {
+    // (the quotient by the host's reciprocal, whose estimate is at most one too
+    // small: an integer division costs about 40 instructions before the first
+    // load can be issued)
+    const unsigned n = (unsigned)item;
     unsigned quo = __umulhi(n, a.strip_rcp);
     if (n - quo * (unsigned)a.nstrips >= (unsigned)a.nstrips) ++quo;
     const int strip = (int)(n - quo * (unsigned)a.nstrips);
-    const int segi = shared ? 4 * (int)quo + wv : (int)quo;
+    const int segi = shared ? 4 * (int)quo + wv : seg0 + (int)quo;
     const int x = strip * a.wout - 2 + lane;
     // x <= nx + 60: within one period unless the lattice is narrow
     const int gx = nx >= 62 ? ghost_near(x, nx, a.bcx) : ghost(x, nx, a.bcx);
@@ -784,15 +787,13 @@ Geom2D geom2d(int nx, int ny, int seg, int ncu, bool share) {
     const long long want = (long long)(-g.seg) * 4 * (ncu > 0 ? ncu : 1) / g.nstrips;
     g.nsegs = (int)std::max(1LL, std::min((long long)ny, want));
   }
-  // shared segments need a multiple of 4 of them (rounded down for a number
-  // of waves, up for a number of rows) and rows enough
-  const int n4 = g.seg > 0 ? (g.nsegs + 3) / 4 * 4 : g.nsegs / 4 * 4;
-  g.shared = share && n4 > 0 && ny / n4 >= kMinRowsShared2D ? 1 : 0;
-  if (g.shared) g.nsegs = n4;
   g.segbase = ny / g.nsegs;
   g.segrem = ny % g.nsegs;
-  int waves = g.nstrips * g.nsegs;
-  g.blocks = (waves + 3) / 4;
+  // as many segments as were asked for: those that make groups of four share
+  // their junctions where each has rows enough
+  g.sharedsegs = share && g.segbase >= kMinRowsShared2D ? g.nsegs / 4 * 4 : 0;
+  g.nshared = g.nstrips * (g.sharedsegs / 4);
+  g.blocks = g.nshared + (g.nstrips * (g.nsegs - g.sharedsegs) + 3) / 4;
   return g;
 }
 

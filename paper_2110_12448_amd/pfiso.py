@@ -36,7 +36,8 @@ PF_DIV_SHELLS, PF_DIV_TWO_POINT = 0, 1
 EXPORTED = ("pf_version", "pf_last_error", "pf_stable_dt", "pf_workspace_bytes", "pf_create",
             "pf_step", "pf_step_diffusion", "pf_synchronize", "pf_read_fields", "pf_tip_state",
             "pf_tip_fields", "pf_device_fields",
-            "pf_frame_state", "pf_tune", "pf_autotune", "pf_geometry", "pf_destroy", "pf_batch_create",
+            "pf_frame_state", "pf_tune", "pf_autotune", "pf_geometry", "pf_launch_waves",
+            "pf_destroy", "pf_batch_create",
             "pf_batch_step", "pf_batch_use_graph", "pf_batch_autotune", "pf_batch_destroy")
 
 
@@ -103,6 +104,7 @@ def load(path: str = LIB_PATH):
     lib.pf_tune.argtypes = [C.c_void_p, C.c_int32, C.c_int32]
     lib.pf_autotune.argtypes = [C.c_void_p, C.c_int32, P(C.c_int32), P(C.c_int32)]
     lib.pf_geometry.argtypes = [C.c_void_p, P(C.c_int32), P(C.c_int32)]
+    lib.pf_launch_waves.argtypes = [C.c_void_p, P(C.c_int64)]
     lib.pf_destroy.argtypes = [C.c_void_p]
     lib.pf_destroy.restype = None
     lib.pf_batch_create.argtypes = [P(C.c_void_p), C.c_int32, P(C.c_void_p)]
@@ -114,7 +116,7 @@ def load(path: str = LIB_PATH):
     for name in ("pf_create", "pf_step", "pf_synchronize", "pf_read_fields", "pf_tip_state",
                  "pf_tip_fields",
                  "pf_device_fields", "pf_frame_state", "pf_tune", "pf_autotune",
-                 "pf_geometry", "pf_batch_create", "pf_batch_step", "pf_batch_use_graph", "pf_batch_autotune"):
+                 "pf_geometry", "pf_launch_waves", "pf_batch_create", "pf_batch_step", "pf_batch_use_graph", "pf_batch_autotune"):
         getattr(lib, name).restype = C.c_int
     _lib = lib
     return lib
@@ -257,6 +259,12 @@ class Solver:
         seg, zt = C.c_int32(), C.c_int32()
         _check(load().pf_geometry(self.handle, C.byref(seg), C.byref(zt)))
         return seg.value, zt.value
+
+    def launch_waves(self):
+        """Waves of one step launch at the geometry in use."""
+        n = C.c_int64()
+        _check(load().pf_launch_waves(self.handle, C.byref(n)))
+        return n.value
 
     def autotune(self, steps_per_trial: int = 10):
         """Time the candidate launch geometries on a scratch copy of the state
