@@ -309,6 +309,10 @@ int pf_batch_create(pf_solver *const *solvers, int32_t n, pf_batch **out);
  * synchronisation). */
 int pf_batch_step(pf_batch *b, int64_t nsteps);
 
+/* Waves that one launch of the batch runs (as pf_launch_waves, over all
+ * members).  PF_ERR_ARG for a NULL pointer. */
+int pf_batch_launch_waves(pf_batch *b, int64_t *waves);
+
 /* Capture steps_per_graph launches (a multiple of 2; of 6 with the moving
  * frame) into a HIP graph replayed by pf_batch_step; 0 launches directly. */
 int pf_batch_use_graph(pf_batch *b, int32_t steps_per_graph);
@@ -316,8 +320,10 @@ int pf_batch_use_graph(pf_batch *b, int32_t steps_per_graph);
 /* Batch autotuner: time the batched step for one segment length shared by
  * every member (4..32 rows) against the one in use (initially each member's
  * own segment length, at least 8 rows; for a member whose geometry asks for
- * waves per SIMD, the longest segment that gives alone, at least 8, 20 or 32
- * rows by the size of the whole batch) over steps_per_trial steps on scratch
+ * waves per SIMD, the longest segment that gives alone, at least 8 rows too,
+ * or for a member whose geometry was never set by pf_tune or pf_autotune at
+ * least 8, 20 or 32 rows by the size of the whole batch; ceil(ny / rows)
+ * segments in each case) over steps_per_trial steps on scratch
  * copies of all member workspaces, with the same passes and margins as pf_autotune,
  * then rebuild the batch with the choice (kept until the batch is destroyed;
  * it overrides the members' own pf_tune settings inside the batch only).  The

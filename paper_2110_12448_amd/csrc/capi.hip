@@ -90,7 +90,7 @@ int default_seg2d(int nx, int ny, int precision, int ncu) {
 }
 // Batched members keep segments of at least 8 rows: the batch fills the chip
 // by itself.  A segment repeats about 3 rows of work, so members that nobody
-// tuned take 20 rows from 60 strip rows per SIMD in the whole batch on, and 32
+// tuned (by pf_tune or pf_autotune) take 20 rows from 60 strip rows per SIMD in the whole batch on, and 32
 // from 160 on; below 60 that would leave SIMDs idle.  us a step with 8 / 20 / 32
 // rows, FP32 (FP64), sides and strip rows R per SIMD:
 //    16 of 100-400,  R  20:  12.7 /  17.4 /  19.2  (23.5 / 30.2 / 29.9)
@@ -309,6 +309,7 @@ struct pf_solver {
   int fcur;   // current frame record (0..2, advances with the frame on)
   long long step;
   int seg, ztile;  // launch geometry (2D seg < 0: -(waves per SIMD))
+  bool tuned;      // seg was set by pf_tune or pf_autotune
   int ncu;         // compute units of the device the solver was created on
   bool have_prev;
   double prev_t, prev_y;
@@ -604,7 +605,8 @@ struct pf_batch {
   int2 *map;    // device workgroup map
   int blocks;
   std::vector<long long> expect;  // solver steps the device table assumes
-  std::vector<int> seg;           // segment lengths the table was built with
+  std::vector<int> seg;           // batch_key of the members the table was built with
+  long long waves;                // waves of one launch
   int graph_steps;
   int seg_fixed;  // > 0: rows per segment of every member (pf_batch_autotune)
   hipStream_t cap;
@@ -620,6 +622,10 @@ int xcd_remap_host(int b, int nb) {
   return x * q + (x < r ? x : r) + b / X;
 }
 
+// What the batch's geometry takes from a member: the segment length it was tuned
+// to, 0 if nobody tuned it.
+int batch_key(const pf_solver *s) { return s->tuned ? s->seg : 0; }
+
 // (Re)build the device table and workgroup map from the solvers' state.
 template <typename T>
 int batch_build(pf_batch *b) {
@@ -630,12 +636,13 @@ int batch_build(pf_batch *b) {
   for (const pf_solver *s : b->s)
     R += (double)((s->p.nx + 59) / 60) * s->p.ny / (4.0 * std::max(1, s->ncu));
   const int rows = batch_rows2d(R);
+  long long waves = 0;
   for (int i = 0; i < n; ++i) {
     pf_solver *s = b->s[i];
     BatchSolve2D<T> &e = tab[i];
     memset(&e, 0, sizeof(e));
     const int seg = b->seg_fixed > 0 ? b->seg_fixed
-                                     : std::max(rows2d(s), s->seg > 0 ? kMinSegBatch2D : rows);
+                                     : std::max(rows2d(s), s->tuned ? kMinSegBatch2D : rows);
     const Geom2D g = geom2d(s->p.nx, s->p.ny, seg, 0, true);
     fill2d<T>(s, e.a, g);
     for (int k = 0; k < 2; ++k) {
@@ -647,8 +654,9 @@ int batch_build(pf_batch *b) {
     e.par0 = s->cur;
     e.f0 = s->fcur;
     for (int lb = 0; lb < g.blocks; ++lb) list.push_back(int2{i, lb});
+    waves += (long long)g.nstrips * g.nsegs;
     b->expect[i] = s->step;
-    b->seg[i] = s->seg;
+    b->seg[i] = batch_key(s);
   }
   const int total = (int)list.size();
   std::vector<int2> map(total);
@@ -663,6 +671,7 @@ int batch_build(pf_batch *b) {
   PF_HIP(hipMemcpy(b->table, tab.data(), sizeof(BatchSolve2D<T>) * n, hipMemcpyHostToDevice));
   PF_HIP(hipMemcpy(b->map, map.data(), sizeof(int2) * total, hipMemcpyHostToDevice));
   b->blocks = total;
+  b->waves = waves;
   return PF_OK;
 }
 
@@ -687,17 +696,21 @@ int batch_capture(pf_batch *b) {
   return PF_OK;
 }
 
+// Rebuild the table (and the graph) if a member was stepped or tuned on its own.
 template <typename T>
-int batch_step(pf_batch *b, long long nsteps) {
+int batch_refresh(pf_batch *b) {
   bool stale = false;
   for (size_t i = 0; i < b->s.size(); ++i)
-    if (b->s[i]->step != b->expect[i] || b->s[i]->seg != b->seg[i]) stale = true;
-  if (stale) {
-    int rc = batch_build<T>(b);
-    if (rc != PF_OK) return rc;
-    rc = batch_capture<T>(b);
-    if (rc != PF_OK) return rc;
-  }
+    if (b->s[i]->step != b->expect[i] || batch_key(b->s[i]) != b->seg[i]) stale = true;
+  if (!stale) return PF_OK;
+  const int rc = batch_build<T>(b);
+  return rc != PF_OK ? rc : batch_capture<T>(b);
+}
+
+template <typename T>
+int batch_step(pf_batch *b, long long nsteps) {
+  const int rc = batch_refresh<T>(b);
+  if (rc != PF_OK) return rc;
   auto *tab = reinterpret_cast<BatchSolve2D<T> *>(b->table);
   long long done = 0;
   if (b->gexec) {
@@ -844,6 +857,7 @@ int autotune_impl(pf_solver *s, int steps) {
   if (k < 0) return fail(PF_ERR_DEVICE, "autotune trial failed");
   s->seg = cand[k].first;
   s->ztile = cand[k].second;
+  s->tuned = true;
   return PF_OK;
 }
 
@@ -954,6 +968,14 @@ int pf_batch_step(pf_batch *b, int64_t nsteps) {
   if (!b) return fail(PF_ERR_ARG, "batch is NULL");
   if (nsteps < 0) return fail(PF_ERR_ARG, "nsteps must be >= 0");
   return b->precision == PF_F64 ? batch_step<double>(b, nsteps) : batch_step<float>(b, nsteps);
+}
+
+int pf_batch_launch_waves(pf_batch *b, int64_t *waves) {
+  if (!b || !waves) return fail(PF_ERR_ARG, "batch or waves is NULL");
+  const int rc = b->precision == PF_F64 ? batch_refresh<double>(b) : batch_refresh<float>(b);
+  if (rc != PF_OK) return rc;
+  *waves = b->waves;
+  return PF_OK;
 }
 
 int pf_batch_use_graph(pf_batch *b, int32_t steps_per_graph) {
@@ -1072,6 +1094,7 @@ int pf_create(const pf_params *p, const pf_init *init, void *workspace, size_t w
   s->fcur = 0;
   s->step = 0;
   s->have_prev = false;
+  s->tuned = false;
   if (workspace) {
     if (workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(workspace) & 255u)) {
       delete s;
@@ -1249,6 +1272,7 @@ int pf_tune(pf_solver *s, int32_t rows_per_segment, int32_t z_tile) {
   if (!s) return fail(PF_ERR_ARG, "solver is NULL");
   if (s->p.dim == 2 && rows_per_segment >= -64 && rows_per_segment <= -1) {
     s->seg = rows_per_segment;  // -k: k waves per SIMD
+    s->tuned = true;
     return PF_OK;
   }
   if (rows_per_segment < 4 || rows_per_segment > 256)
@@ -1262,6 +1286,7 @@ int pf_tune(pf_solver *s, int32_t rows_per_segment, int32_t z_tile) {
       step3d_lds_bytes(s->p.nx, z_tile, s->p.precision == PF_F64 ? 8 : 4) > kMaxLds3D)
     return fail(PF_ERR_ARG, "z_tile too large for the LDS of one workgroup at this precision");
   s->seg = rows_per_segment;
+  s->tuned = true;
   if (s->p.dim == 3) s->ztile = z_tile;
   return PF_OK;
 }

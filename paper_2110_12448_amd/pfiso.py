@@ -38,7 +38,8 @@ EXPORTED = ("pf_version", "pf_last_error", "pf_stable_dt", "pf_workspace_bytes",
             "pf_tip_fields", "pf_device_fields",
             "pf_frame_state", "pf_tune", "pf_autotune", "pf_geometry", "pf_launch_waves",
             "pf_destroy", "pf_batch_create",
-            "pf_batch_step", "pf_batch_use_graph", "pf_batch_autotune", "pf_batch_destroy")
+            "pf_batch_step", "pf_batch_launch_waves", "pf_batch_use_graph", "pf_batch_autotune",
+            "pf_batch_destroy")
 
 
 class pf_params(C.Structure):
@@ -109,6 +110,7 @@ def load(path: str = LIB_PATH):
     lib.pf_destroy.restype = None
     lib.pf_batch_create.argtypes = [P(C.c_void_p), C.c_int32, P(C.c_void_p)]
     lib.pf_batch_step.argtypes = [C.c_void_p, C.c_int64]
+    lib.pf_batch_launch_waves.argtypes = [C.c_void_p, P(C.c_int64)]
     lib.pf_batch_use_graph.argtypes = [C.c_void_p, C.c_int32]
     lib.pf_batch_autotune.argtypes = [C.c_void_p, C.c_int32, P(C.c_int32)]
     lib.pf_batch_destroy.argtypes = [C.c_void_p]
@@ -116,7 +118,8 @@ def load(path: str = LIB_PATH):
     for name in ("pf_create", "pf_step", "pf_synchronize", "pf_read_fields", "pf_tip_state",
                  "pf_tip_fields",
                  "pf_device_fields", "pf_frame_state", "pf_tune", "pf_autotune",
-                 "pf_geometry", "pf_launch_waves", "pf_batch_create", "pf_batch_step", "pf_batch_use_graph", "pf_batch_autotune"):
+                 "pf_geometry", "pf_launch_waves", "pf_batch_create", "pf_batch_step",
+                 "pf_batch_launch_waves", "pf_batch_use_graph", "pf_batch_autotune"):
         getattr(lib, name).restype = C.c_int
     _lib = lib
     return lib
@@ -300,6 +303,12 @@ class Batch:
 
     def use_graph(self, steps_per_graph: int):
         _check(load().pf_batch_use_graph(self.handle, int(steps_per_graph)))
+
+    def launch_waves(self):
+        """Waves of one launch of the batch."""
+        n = C.c_int64()
+        _check(load().pf_batch_launch_waves(self.handle, C.byref(n)))
+        return n.value
 
     def step(self, nsteps: int = 1):
         _check(load().pf_batch_step(self.handle, int(nsteps)))
