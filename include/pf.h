@@ -267,6 +267,14 @@ int pf_geometry(pf_solver *s, int32_t *rows_per_segment, int32_t *z_tile);
  * geometry: no part of the paper's method).  PF_ERR_ARG for a NULL pointer. */
 int pf_launch_waves(pf_solver *s, int64_t *waves);
 
+/* The same for a solve that nobody tuned, before it is created and without a
+ * device: waves of one launch on a device of `cus` compute units, of the solve on
+ * its own (batch_load < 0) or of its part of a batch (2D) whose members have
+ * batch_load strip rows per SIMD in all, the sum of ceil(nx / 60) * ny over 4 *
+ * cus.  PF_ERR_ARG for invalid parameters, cus < 1, a NULL pointer or a batched
+ * 3D solve. */
+int pf_default_waves(const pf_params *p, int32_t cus, double batch_load, int64_t *waves);
+
 /* Tile autotuner: time each candidate launch geometry (2D: 1..32 waves per
  * SIMD, as pf_tune's -k; 3D: rows per segment 8..256 times z rows per workgroup, within the
  * LDS of one workgroup and at most 6 z rows in FP64) over steps_per_trial

@@ -317,12 +317,32 @@ struct pf_solver {
 
 namespace {
 
-// Rows per segment of the solver's 2D geometry (the longest segment when it
-// asks for waves per SIMD).
-int rows2d(const pf_solver *s) {
-  if (s->seg > 0) return s->seg;
-  const Geom2D g = geom2d(s->p.nx, s->p.ny, s->seg, s->ncu, false);
-  return g.segbase + (g.segrem ? 1 : 0);
+// The library's launch geometry of a problem nobody tuned: (rows per segment or
+// -(waves per SIMD), z rows per workgroup).
+std::pair<int, int> default_geom(const pf_params *p, int ncu) {
+  if (p->dim == 2) return {default_seg2d(p->nx, p->ny, p->precision, ncu), 1};
+  return default_geom3d(p, ncu);
+}
+
+// Waves of one step launch at the geometry (seg, ztile).
+int64_t solo_waves(const pf_params &p, int seg, int ztile, int ncu) {
+  if (p.dim == 2) {
+    const Geom2D g = geom2d(p.nx, p.ny, seg, ncu, true);
+    return (int64_t)g.nstrips * g.nsegs;
+  }
+  const Geom3D g = geom3d(p.nx, p.ny, p.nz, seg, ztile);
+  return (int64_t)g.blocks * (g.threads / 64);
+}
+
+// Geometry of a batch member whose own is seg: its rows per segment (the longest
+// segment when it asks for waves per SIMD), but at least min_rows.
+Geom2D member_geom2d(const pf_params &p, int seg, int ncu, int min_rows) {
+  int rows = seg;
+  if (seg < 0) {
+    const Geom2D g = geom2d(p.nx, p.ny, seg, ncu, true);
+    rows = g.segbase + (g.segrem ? 1 : 0);
+  }
+  return geom2d(p.nx, p.ny, std::max(rows, min_rows), 0, true);
 }
 
 template <typename T>
@@ -641,9 +661,9 @@ int batch_build(pf_batch *b) {
     pf_solver *s = b->s[i];
     BatchSolve2D<T> &e = tab[i];
     memset(&e, 0, sizeof(e));
-    const int seg = b->seg_fixed > 0 ? b->seg_fixed
-                                     : std::max(rows2d(s), s->tuned ? kMinSegBatch2D : rows);
-    const Geom2D g = geom2d(s->p.nx, s->p.ny, seg, 0, true);
+    const Geom2D g = b->seg_fixed > 0
+                         ? geom2d(s->p.nx, s->p.ny, b->seg_fixed, 0, true)
+                         : member_geom2d(s->p, s->seg, s->ncu, s->tuned ? kMinSegBatch2D : rows);
     fill2d<T>(s, e.a, g);
     for (int k = 0; k < 2; ++k) {
       e.psi[k] = field<T>(s, s->L.psi[k]);
@@ -1122,12 +1142,7 @@ int pf_create(const pf_params *p, const pf_init *init, void *workspace, size_t w
         s->ncu < 1)
       r2 = fail(PF_ERR_DEVICE, "cannot read the device's compute unit count");
   }
-  if (p->dim == 2) {
-    s->seg = default_seg2d(p->nx, p->ny, p->precision, s->ncu);
-    s->ztile = 1;
-  } else {
-    std::tie(s->seg, s->ztile) = default_geom3d(p, s->ncu);
-  }
+  std::tie(s->seg, s->ztile) = default_geom(p, s->ncu);
   if (r2 == PF_OK)
     r2 = p->precision == PF_F64 ? upload<double>(s, init) : upload<float>(s, init);
   if (r2 == PF_OK && p->n_grains > 1) {
@@ -1293,14 +1308,22 @@ int pf_tune(pf_solver *s, int32_t rows_per_segment, int32_t z_tile) {
 
 int pf_launch_waves(pf_solver *s, int64_t *waves) {
   if (!s || !waves) return fail(PF_ERR_ARG, "solver or waves is NULL");
-  const pf_params &p = s->p;
-  if (p.dim == 2) {
-    const Geom2D g = geom2d(p.nx, p.ny, s->seg, s->ncu, true);
-    *waves = (int64_t)g.nstrips * g.nsegs;
-  } else {
-    const Geom3D g = geom3d(p.nx, p.ny, p.nz, s->seg, s->ztile);
-    *waves = (int64_t)g.blocks * (g.threads / 64);
+  *waves = solo_waves(s->p, s->seg, s->ztile, s->ncu);
+  return PF_OK;
+}
+
+int pf_default_waves(const pf_params *p, int32_t cus, double batch_load, int64_t *waves) {
+  const int rc = validate(p);
+  if (rc != PF_OK) return rc;
+  if (!waves || cus < 1) return fail(PF_ERR_ARG, "need cus >= 1 and a waves pointer");
+  const auto geo = default_geom(p, cus);
+  if (!(batch_load >= 0.0)) {
+    *waves = solo_waves(*p, geo.first, geo.second, cus);
+    return PF_OK;
   }
+  if (p->dim != 2) return fail(PF_ERR_ARG, "batched stepping is 2D only");
+  const Geom2D g = member_geom2d(*p, geo.first, cus, batch_rows2d(batch_load));
+  *waves = (int64_t)g.nstrips * g.nsegs;
   return PF_OK;
 }
 

@@ -37,7 +37,7 @@ EXPORTED = ("pf_version", "pf_last_error", "pf_stable_dt", "pf_workspace_bytes",
             "pf_step", "pf_step_diffusion", "pf_synchronize", "pf_read_fields", "pf_tip_state",
             "pf_tip_fields", "pf_device_fields",
             "pf_frame_state", "pf_tune", "pf_autotune", "pf_geometry", "pf_launch_waves",
-            "pf_destroy", "pf_batch_create",
+            "pf_default_waves", "pf_destroy", "pf_batch_create",
             "pf_batch_step", "pf_batch_launch_waves", "pf_batch_use_graph", "pf_batch_autotune",
             "pf_batch_destroy")
 
@@ -106,6 +106,7 @@ def load(path: str = LIB_PATH):
     lib.pf_autotune.argtypes = [C.c_void_p, C.c_int32, P(C.c_int32), P(C.c_int32)]
     lib.pf_geometry.argtypes = [C.c_void_p, P(C.c_int32), P(C.c_int32)]
     lib.pf_launch_waves.argtypes = [C.c_void_p, P(C.c_int64)]
+    lib.pf_default_waves.argtypes = [P(pf_params), C.c_int32, C.c_double, P(C.c_int64)]
     lib.pf_destroy.argtypes = [C.c_void_p]
     lib.pf_destroy.restype = None
     lib.pf_batch_create.argtypes = [P(C.c_void_p), C.c_int32, P(C.c_void_p)]
@@ -118,7 +119,7 @@ def load(path: str = LIB_PATH):
     for name in ("pf_create", "pf_step", "pf_synchronize", "pf_read_fields", "pf_tip_state",
                  "pf_tip_fields",
                  "pf_device_fields", "pf_frame_state", "pf_tune", "pf_autotune",
-                 "pf_geometry", "pf_launch_waves", "pf_batch_create", "pf_batch_step",
+                 "pf_geometry", "pf_launch_waves", "pf_default_waves", "pf_batch_create", "pf_batch_step",
                  "pf_batch_launch_waves", "pf_batch_use_graph", "pf_batch_autotune"):
         getattr(lib, name).restype = C.c_int
     _lib = lib

@@ -70,61 +70,23 @@ def _batchable(prob: dict) -> bool:
     return prob["dim"] == 2 and not prob.get("antitrapping", 0) and not prob.get("two_point", 0)
 
 
-def _geom3d_blocks(nx: int, ny: int, nz: int, seg: int, ztile: int) -> int:
-    """Workgroups of one 3D step launch (the library's tile layout: strips of
-    60 columns, the nx mod 60 remainder as a thin strip of 3 lane groups (13
-    to 17 columns) or 4 (up to 12) with (ztile + 2) * groups - 2 z rows per
-    tile, z tiles of ztile rows, segments of at most seg rows, 3/4 of that in
-    the thin strip)."""
-    nw = ztile + 2
-    nfull, r = nx // 60, nx % 60
-    gr = 0 if r == 0 else (4 if r <= 12 else (3 if r <= 17 else 1))
-    thin_nzt = 0
-    if r == 0 or gr >= 3:
-        nstrips = nfull
-        if r > 0:
-            thin_nzt = -(-nz // (nw * gr - 2))
-    else:
-        nstrips = -(-nx // 60)
-    thin_nsegs = -(-ny // max(1, seg * 3 // 4)) if thin_nzt else 0
-    return nstrips * -(-nz // ztile) * -(-ny // seg) + thin_nzt * thin_nsegs
+def strip_rows(prob: dict) -> int:
+    """Rows of all 60-column strips of a 2D solve: what a batch's size is counted in."""
+    return -(-int(prob["nx"]) // 60) * int(prob["ny"])
 
 
-def estimated_waves(prob: dict, batched: bool = False, cus: int = 256) -> int:
+def estimated_waves(prob: dict, batched: bool = False, cus: int = 256,
+                    precision: int = pfiso.PF_F32, load: float = 0.0) -> int:
     """Waves one step launch of this solve occupies at the library's default
-    FP32 geometry on a device of `cus` compute units: the measure of how much
-    of the chip a solve fills.  60 output columns per wave; in 2D k =
-    round(R^0.4) waves per SIMD with R = strips * ny / SIMDs, at most one
-    segment per row, and inside a batch segments of that length but at least
-    8 rows; in 3D workgroups of 14, 6 or 2 z rows (16, 8 or 4 waves) with
-    the segment count that minimises rounds x (rows + 2.5) x (1 + 0.43 waves
-    per SIMD), as the library's default."""
-    strips = -(-prob["nx"] // 60)
-    if prob["dim"] == 2:
-        ny, simds = prob["ny"], 4 * cus
-        k = max(1, int(np.floor((strips * ny / simds) ** 0.4 + 0.5)))
-        nsegs = max(1, min(ny, k * simds // strips))
-        if batched:
-            nsegs = -(-ny // max(8, -(-ny // nsegs)))
-        return strips * nsegs
-    nx, ny, nz = prob["nx"], prob["ny"], prob["nz"]
-    best, best_cost, last = 0, None, 0
-    for want in (14, 6, 2):
-        zt = min(want, nz)
-        if zt == last:
-            continue
-        last, nw, per_cu = zt, zt + 2, 16 // (zt + 2)
-        blocks_zt, cost_zt = 0, None
-        for n in range(1, max(1, ny // 4) + 1):
-            rows = -(-ny // n)
-            blocks = _geom3d_blocks(nx, ny, nz, rows, zt)
-            w = min(per_cu, -(-blocks // cus)) * nw / 4.0
-            cost = -(-blocks // (cus * per_cu)) * (rows + 2.5) * (1.0 + 0.43 * w)
-            if cost_zt is None or cost < cost_zt - 1e-9:
-                blocks_zt, cost_zt = blocks, cost
-        if best_cost is None or cost_zt < 0.95 * best_cost:
-            best, best_cost = blocks_zt * nw, cost_zt
-    return best
+    geometry on a device of `cus` compute units (pf_default_waves): the measure
+    of how much of the chip a solve fills.  batched: its part of a batch whose
+    members have `load` strip rows per SIMD in all (the larger the batch, the
+    longer the segments its members take)."""
+    p, keep = pfiso.make_params(prob, precision)
+    n = C.c_int64()
+    pfiso._check(pfiso.load().pf_default_waves(C.byref(p), int(cus),
+                                               float(load) if batched else -1.0, C.byref(n)))
+    return n.value
 
 
 def _work(r: Request) -> int:
@@ -147,7 +109,28 @@ class _Active:
     admitted: float
     done: int = 0
     nbytes: int = 0
-    waves: int = 0
+    kind: Optional[tuple] = None     # batch kind, None for a solve launched on its own
+    waves: int = 0                   # of a solve launched on its own
+
+
+def _occupied(active: List[_Active], batch_seg: Dict[tuple, int], cus: int) -> int:
+    """Waves that one step of all active solves launches.  The members of a batch
+    are counted at the rows they take in it: those it was tuned to (batch_seg, at
+    least 8), or the library's by the size of the whole batch."""
+    total = sum(a.waves for a in active if a.kind is None)
+    groups: Dict[tuple, List[_Active]] = {}
+    for a in active:
+        if a.kind is not None:
+            groups.setdefault(a.kind, []).append(a)
+    for kind, members in groups.items():
+        rows = batch_seg.get(kind, 0)
+        load = sum(strip_rows(m.req.problem) for m in members) / (4.0 * cus)
+        for m in members:
+            pr = m.req.problem
+            total += (-(-int(pr["nx"]) // 60) * -(-int(pr["ny"]) // max(8, rows)) if rows else
+                      estimated_waves(pr, batched=True, cus=cus, precision=m.req.precision,
+                                      load=load))
+    return total
 
 
 class Server:
@@ -156,7 +139,8 @@ class Server:
                  progress: int = 0, max_waves: Optional[int] = None, streams: int = 1,
                  autotune_steps: int = 0, order: str = "fifo"):
         """max_waves: admit a request only while the active solves occupy fewer
-        waves than this (estimated_waves; None: the HBM budget alone decides).
+        waves than this (as the library launches them; None: the HBM budget
+        alone decides).
         streams: HIP streams the solves are spread over (batched solves share
         the first, the others take the rest in turn), so that launches of
         solves too small to fill the chip can run side by side.
@@ -199,7 +183,7 @@ class Server:
         turn = 0
         geo: Dict[tuple, tuple] = {}      # shape class -> (rows per segment, z rows)
         batch_seg: Dict[tuple, int] = {}  # batch kind -> rows per segment (0: members' own)
-        waves = 0
+        cus = torch.cuda.get_device_properties(dev).multi_processor_count
 
         def now():
             return time.perf_counter() - t0 + skew
@@ -218,7 +202,8 @@ class Server:
                 need = workspace_bytes(r.problem, r.precision)
                 if used + need > self.budget and active:
                     break
-                if self.max_waves is not None and waves >= self.max_waves and active:
+                if (self.max_waves is not None and active and
+                        _occupied(active, batch_seg, cus) >= self.max_waves):
                     break
                 queue.pop(0)
                 batched = self.batching and _batchable(r.problem)
@@ -234,10 +219,10 @@ class Server:
                         geo[cls] = s.autotune(self.autotune_steps)
                     else:
                         s.tune(*geo[cls])
-                active.append(_Active(r, s, now(), 0, need, estimated_waves(
-                    r.problem, batched=self.batching and _batchable(r.problem))))
+                active.append(_Active(r, s, now(), 0, need,
+                                      _kind(r.problem, r.precision) if batched else None,
+                                      s.launch_waves()))
                 used += need
-                waves += active[-1].waves
             if not active:
                 if pending:
                     wait = pending[0].arrival - now()
@@ -252,8 +237,8 @@ class Server:
             tb = time.perf_counter()
             groups: Dict[tuple, List[_Active]] = {}
             for a in active:
-                if self.batching and _batchable(a.req.problem):
-                    groups.setdefault(_kind(a.req.problem, a.req.precision), []).append(a)
+                if a.kind is not None:
+                    groups.setdefault(a.kind, []).append(a)
             for kind, members in groups.items():
                 rids = tuple(m.req.rid for m in members)
                 if kind not in batches or batches[kind][0] != rids:
@@ -272,7 +257,7 @@ class Server:
             for kind in [k for k in batches if k not in groups]:
                 batches.pop(kind)[1].close()
             for a in active:
-                if not (self.batching and _batchable(a.req.problem)):
+                if a.kind is None:
                     a.solver.step(tick)
                 a.done += tick
             torch.cuda.synchronize()
@@ -299,7 +284,6 @@ class Server:
                         batches.pop(kind)[1].close()
                 a.solver.close()
                 used -= a.nbytes
-                waves -= a.waves
             active = still
         for _, b in batches.values():
             b.close()
