@@ -44,15 +44,17 @@ namespace {
   } while (0)
 
 // Run f(begin, end) over the pieces of [0, n) on up to kHostThreads threads
-// (the caller's among them), at least `grain` items each.  The hand-over of the
+// (the caller's among them), at least `grain` items each; fewer than `least`
+// pieces run in the calling thread alone.  The hand-over of the
 // fields between the caller's FP64 arrays and the device's is bound by one
 // core's conversions, page faults and tanh: with 8 threads pf_read_fields of
 // 1024x2048 FP32 takes 3.9 ms instead of 11.0.  f must not throw.  A thread that cannot be
 // started leaves its piece to the caller's.
 constexpr size_t kHostThreads = 8;
 template <typename F>
-void host_parallel(size_t n, size_t grain, F f) {
-  size_t k = std::max<size_t>(1, std::min(kHostThreads, n / grain));
+void host_parallel(size_t n, size_t grain, size_t least, F f) {
+  size_t k = std::min(kHostThreads, n / grain);
+  if (k < least) k = 1;
   if (k > 1) k = std::min<size_t>(k, std::max(1u, std::thread::hardware_concurrency()));
   if (k == 1) return f(0, n);
   auto piece = [&](size_t i) { f(n * i / k, n * (i + 1) / k); };
@@ -70,6 +72,12 @@ void host_parallel(size_t n, size_t grain, F f) {
 // where starting threads for less costs more than they save (700^2 with 7
 // threads of 64k cells 640 -> 780 us).
 constexpr size_t kHostGrain = 1 << 16, kHostGrainIn = 1 << 18;
+// and pieces it takes at least.  pf_create in us, in the calling thread alone /
+// in pieces (some runs put two threads where they share little and take half as
+// long again): FP32 760^2 815 / 2 pieces 850, 900^2 1230 / 3 pieces 1130; FP64
+// 760^2 950 / 2 pieces 1360, 900^2 1430 / 3 pieces 1600, 1024^2 2200 / 4 pieces
+// 2200 (after a read-back by threads 2450 / 2010).
+constexpr size_t least_pieces_in(size_t elem) { return elem == 4 ? 3 : 4; }
 
 // thin-interface constant a2 = 47/75 (Sec. 2.1): default lambda = D~ / a2
 constexpr double kA2 = 47.0 / 75.0;
@@ -435,9 +443,16 @@ int upload(pf_solver *s, const pf_init *init) {
   std::unique_ptr<T[]> buf(new (std::nothrow) T[n]);
   if (!buf) return fail(PF_ERR_OOM, "host allocation failed");
   T *tmp = buf.get();
+  // FP32 in the calling thread alone: whole lines are written before the
+  // conversions store into them, because after a read-back by threads the
+  // buffer's lines are in other cores' caches (pf_create of 512^2 then 570 us
+  // without, 525 with; of 512^2 otherwise 505 and 512).  FP64 ran up to 4%
+  // slower with it, also after a read-back.
+  if (sizeof(T) == 4 && n < least_pieces_in(sizeof(T)) * kHostGrainIn)
+    memset(tmp, 0, n * sizeof(T));
   for (int k = 0; k < 2; ++k) {
     const double *src = k == 0 ? init->psi : init->U;
-    host_parallel(n, kHostGrainIn, [&](size_t b, size_t e) {
+    host_parallel(n, kHostGrainIn, least_pieces_in(sizeof(T)), [&](size_t b, size_t e) {
       for (size_t i = b; i < e; ++i) tmp[i] = (T)src[i];
     });
     PF_HIP(hipMemcpy(field<T>(s, k == 0 ? s->L.psi[0] : s->L.U[0]), tmp, n * sizeof(T),
@@ -599,7 +614,7 @@ int read_impl(pf_solver *s, double *phi, double *U, double *psi) {
   PF_HIP(hipMemcpy(bp.get(), field<T>(s, s->L.psi[s->cur]), n * sizeof(T), hipMemcpyDeviceToHost));
   PF_HIP(hipMemcpy(bu.get(), field<T>(s, s->L.U[s->cur]), n * sizeof(T), hipMemcpyDeviceToHost));
   const size_t nx = p.nx, ny = p.ny, nz = p.dim == 3 ? p.nz : 1;
-  host_parallel(ny * nz, std::max<size_t>(1, kHostGrain / nx), [&](size_t b, size_t e) {
+  host_parallel(ny * nz, std::max<size_t>(1, kHostGrain / nx), 2, [&](size_t b, size_t e) {
     for (size_t row = b; row < e; ++row) {
       const size_t j = row % ny, jp = fr.pending ? std::min(j + 1, ny - 1) : j;
       const size_t dst = row * nx, src = (row - j + jp) * nx;
@@ -1064,8 +1079,9 @@ int pf_create(const pf_params *p, const pf_init *init, void *workspace, size_t w
   if (!init || !init->psi || !init->U) return fail(PF_ERR_ARG, "init arrays are NULL");
   if (!out) return fail(PF_ERR_ARG, "out is NULL");
   const size_t n = cells(p);
+  const size_t least = least_pieces_in(p->precision == PF_F64 ? 8 : 4);
   std::atomic<bool> bad{false};
-  host_parallel(n, kHostGrainIn, [&](size_t b, size_t e) {
+  host_parallel(n, kHostGrainIn, least, [&](size_t b, size_t e) {
     const double *psi = init->psi, *U = init->U;
     int any = 0;  // no branch on a cell, so the loop vectorises (half the time)
     for (size_t i = b; i < e; ++i)
@@ -1074,7 +1090,7 @@ int pf_create(const pf_params *p, const pf_init *init, void *workspace, size_t w
   });
   if (bad.load()) return fail(PF_ERR_NONFINITE, "initial psi or U holds NaN or Inf");
   if (init->grain) {
-    host_parallel(n, kHostGrainIn, [&](size_t b, size_t e) {
+    host_parallel(n, kHostGrainIn, least, [&](size_t b, size_t e) {
       const int8_t *g = init->grain;
       const int ng = p->n_grains;
       int any = 0;
