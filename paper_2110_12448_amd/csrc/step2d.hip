@@ -152,23 +152,31 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 
 // Waves per SIMD the register budget must leave room for.  The steady-state
 // row group is one basic block, so the scheduler overlaps rows freely: FP32
-// variants settle at 85-132 VGPRs (3-5 waves per SIMD) and run fastest
-// unconstrained; the FP64 approximated-current single-grain variants would
-// take 200+ VGPRs (2 waves) and run 6-18% faster held to 3 waves (168 VGPRs,
-// no spills).  The other FP64 variants would spill there and stay
-// unconstrained.
+// variants settle at 65-126 VGPRs (4-7 waves per SIMD) and run fastest
+// unconstrained, but for the full current on shells with several grains, which
+// takes 130 (3 waves: 25.7 us a step on 1024x2048 with the frame, 22.4 held to
+// 4).  The FP64 approximated-current single-grain variants would take 200+
+// VGPRs (2 waves) and run faster held to 3 waves (168 VGPRs, of which up to 26
+// spilled): 1024x2048 with the frame 26.9 us.  The FP64 full current on shells
+// with several grains and the frame goes past 256 (one wave: 61.5 us, 47.0 held
+// to 2), and the single-grain full current on two-point faces takes 240 where
+// 180 do (33.5 -> 29.9 us).
 template <typename T, bool kMulti, int kAT>
 constexpr int kMinWaves2D =
     sizeof(T) == 8 && !kMulti &&
             (kAT == kAtApproxShells || kAT == kAtApproxTwoPoint || kAT == kAtDiffusionOnly)
         ? 3
-        : 1;
+    : sizeof(T) == 8 && (kAT == kAtFullShells || (kAT == kAtFullTwoPoint && !kMulti)) ? 2
+    : sizeof(T) == 4 && kAT == kAtFullShells && kMulti                                ? 4
+                                                                                      : 1;
 // The batched kernel's FP32 variants hold 4 waves per SIMD: unconstrained,
 // its frozen variants settle at 124-132 VGPRs, where the 4th wave comes and
 // goes with small changes to the body; held to 128, two spill a register or
-// two outside the row loop.
-template <typename T, bool kMulti>
-constexpr int kMinWavesBatch2D = sizeof(T) == 4 ? 4 : kMinWaves2D<T, kMulti, kAtApproxShells>;
+// two outside the row loop.  Single-grain ones with the frame fit 5 (89-92
+// VGPRs; at 103 16 solves of 256-1024 took 42.1 us a step instead of 40.8).
+template <typename T, bool kMulti, bool kReduce>
+constexpr int kMinWavesBatch2D = sizeof(T) == 4 ? (kReduce && !kMulti ? 5 : 4)
+                                                : kMinWaves2D<T, kMulti, kAtApproxShells>;
 
 // One logical workgroup `lb` (4 waves) of the step of one solve `a`.
 //
@@ -738,7 +746,7 @@ void step2d_kernel(Step2DArgs<T> a) {
 // n0 + k: buffers and frame records are picked from the epoch's parities.
 template <typename T, bool kFrozen, bool kReduce, bool kMulti>
 __global__ __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(kMinWavesBatch2D<T, kMulti>)))
+    __attribute__((amdgpu_waves_per_eu(kMinWavesBatch2D<T, kMulti, kReduce>)))
 void batch2d_kernel(const BatchSolve2D<T> *table,
                                                       const int2 *map, int k) {
   const int2 bm = map[blockIdx.x];
