@@ -76,11 +76,14 @@ struct Step2DArgs {
   const T *rot;          // multi-grain only: (c2, s2) per grain
   const T *axes;         // (r00, r01, r10, r11) per grain (FP32 full current on shells)
   T c2, s2;              // single grain: cos and sin of twice its angle
-  int nx, ny, bcx, bcy;
-  int wout, nstrips, nsegs, segbase, segrem;
+  // what a wave needs for its place on the lattice lies together: few scalar
+  // loads, waited for once before the first row can be read
+  int nstrips, nsegs;
   unsigned strip_rcp;    // floor(2^32 / nstrips), at most 2^32 - 1
+  int nx, bcx, wout;
   int nshared;           // workgroups whose waves share a strip and their junctions
   int sharedsegs;        // segments of each strip they hold, a multiple of 4
+  int segbase, segrem, ny, bcy;
   Coef<T> c;
   double hd, y0, Vp, dtd, inv_lTd;
   long long step;

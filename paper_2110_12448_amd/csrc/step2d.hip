@@ -207,6 +207,20 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
   const bool shared = !kDiff && lb < a.nshared;
   const bool first = !shared || wv == 0, last = !shared || wv == 3;
 
+  int pend = 0;
+  long long shift = 0;
+  auto read_frame = [&]() {
+    if (kReduce) pend = a.frame_in->pending, shift = a.frame_in->base + pend;
+  };
+  if constexpr (kRowTail) {
+    // solo launches: one wait for all arguments that the first row's address
+    // needs, not one by one (2% of a step on 448^2; batched waves read them from
+    // the table and ran up to 5% slower with it in FP64)
+    read_frame();
+    asm volatile("" ::"s"(a.strip_rcp), "s"(a.wout), "s"(a.bcx), "s"(a.segbase), "s"(a.segrem),
+                 "s"(a.bcy), "s"(a.psi_in), "s"(a.U_in));
+  }
+
   // group of four segments (shared) or segment above the groups, strip fastest
   const int item = shared ? lb : (kDiff ? lb : lb - a.nshared) * 4 + wv;
   const int seg0 = kDiff ? 0 : a.sharedsegs;  // first segment above the groups
@@ -226,8 +240,7 @@ __device__ __forceinline__ void step2d_body(const Step2DArgs<T> &a, const int lb
     // rows split evenly: the first segrem segments take one row more
     const int y0 = segi * a.segbase + min(segi, a.segrem);
     const int ye = y0 + a.segbase + (segi < a.segrem ? 1 : 0);
-    const int pend = a.frame ? a.frame_in->pending : 0;
-    const long long shift = a.frame ? a.frame_in->base + pend : 0;
+    if constexpr (!kRowTail) read_frame();
     T off = T(0), offT = T(0);  // zeta and zeta / lT of row 0
     if (kFrozen && kAxes)
       off = (T)((double)shift * a.hd - a.y0 - a.Vp * ((double)a.step * a.dtd));
