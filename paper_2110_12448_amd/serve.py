@@ -83,9 +83,12 @@ def estimated_waves(prob: dict, batched: bool = False, cus: int = 256,
     members have `load` strip rows per SIMD in all (the larger the batch, the
     longer the segments its members take)."""
     p, keep = pfiso.make_params(prob, precision)
+    return _default_waves(p, cus, float(load) if batched else -1.0)
+
+
+def _default_waves(p: pfiso.pf_params, cus: int, load: float) -> int:
     n = C.c_int64()
-    pfiso._check(pfiso.load().pf_default_waves(C.byref(p), int(cus),
-                                               float(load) if batched else -1.0, C.byref(n)))
+    pfiso._check(pfiso.load().pf_default_waves(C.byref(p), int(cus), load, C.byref(n)))
     return n.value
 
 
@@ -126,10 +129,9 @@ def _occupied(active: List[_Active], batch_seg: Dict[tuple, int], cus: int) -> i
         rows = batch_seg.get(kind, 0)
         load = sum(strip_rows(m.req.problem) for m in members) / (4.0 * cus)
         for m in members:
-            pr = m.req.problem
-            total += (-(-int(pr["nx"]) // 60) * -(-int(pr["ny"]) // max(8, rows)) if rows else
-                      estimated_waves(pr, batched=True, cus=cus, precision=m.req.precision,
-                                      load=load))
+            p = m.solver.params
+            total += (-(-p.nx // 60) * -(-p.ny // max(8, rows)) if rows else
+                      _default_waves(p, cus, load))
     return total
 
 
@@ -221,7 +223,7 @@ class Server:
                         s.tune(*geo[cls])
                 active.append(_Active(r, s, now(), 0, need,
                                       _kind(r.problem, r.precision) if batched else None,
-                                      s.launch_waves()))
+                                      0 if batched else s.launch_waves()))
                 used += need
             if not active:
                 if pending:
