@@ -98,17 +98,17 @@ int default_seg2d(int nx, int ny, int precision, int ncu) {
 }
 // Batched members keep segments of at least 8 rows: the batch fills the chip
 // by itself.  A segment repeats about 3 rows of work, so members that nobody
-// tuned (by pf_tune or pf_autotune) take 20 rows from 60 strip rows per SIMD in the whole batch on, and 32
-// from 160 on; below 60 that would leave SIMDs idle.  us a step with 8 / 20 / 32
-// rows, FP32 (FP64), sides and strip rows R per SIMD:
-//    16 of 100-400,  R  20:  12.7 /  17.4 /  19.2  (23.5 / 30.2 / 29.9)
-//    16 of 150-600,  R  43:  21.1 /  22.8 /  24.9  (38.7 / 39.9 / 42.4)
-//     8 of 256-1024, R  62:  27.5 /  27.4 /  31.2  (52.9 / 51.1 / 56.4)
-//    16 of 200-800,  R  75:  29.8 /  27.5 /  31.7  (58.7 / 51.5 / 57.3)
-//    12 of 300-900,  R  78:  31.8 /  32.5 /  31.8  (63.0 / 60.7 / 57.1)
-//    16 of 256-1024, R 122:  44.1 /  41.5 /  45.8  (101.5 / 89.7 / 93.8)
-//    32 of 256-1024, R 242:  80.6 /  75.1 /  76.1  (215.1 / 184.6 / 178.1)
-//    64 of 256-1024, R 483: 179.6 / 154.6 / 146.3  (416.4 / 350.1 / 325.9)
+// tuned (by pf_tune or pf_autotune) take 20 rows from 60 strip rows per SIMD in
+// the whole batch on, and 32 from 160 on; below 60 that would leave SIMDs idle.
+// us a step with 8 / 20 / 32 rows, FP32 (FP64), sides and strip rows R per SIMD:
+//    16 of 100-400,  R  20:  12.8 /  16.6 /  19.5  (23.9 / 29.3 / 29.0)
+//    16 of 150-600,  R  43:  20.4 /  22.5 /  24.7  (38.3 / 39.5 / 42.3)
+//     8 of 256-1024, R  62:  26.6 /  26.7 /  31.3  (52.8 / 50.2 / 56.2)
+//    16 of 200-800,  R  75:  28.8 /  27.0 /  31.8  (58.5 / 50.4 / 56.6)
+//    12 of 300-900,  R  78:  30.6 /  31.7 /  31.8  (62.4 / 59.8 / 57.1)
+//    16 of 256-1024, R 122:  41.1 /  40.4 /  45.3  (96.4 / 84.6 / 88.6)
+//    32 of 256-1024, R 242:  77.7 /  70.5 /  73.6  (207.6 / 167.1 / 164.9)
+//    64 of 256-1024, R 483: 172.5 / 147.0 / 142.1  (399.0 / 324.0 / 312.6)
 constexpr int kMinSegBatch2D = 8;
 int batch_rows2d(double R) { return R < 60.0 ? kMinSegBatch2D : R < 160.0 ? 20 : 32; }
 constexpr size_t kMaxLds3DBytes = 163840;  // LDS one gfx950 workgroup may allocate
@@ -215,8 +215,15 @@ Layout layout_of(const pf_params *p) {
   size_t es = p->precision == PF_F64 ? 8 : 4;
   size_t n = cells(p);
   size_t o = 0;
-  for (int i = 0; i < 2; ++i) { L.psi[i] = o; o += align256(n * es); }
-  for (int i = 0; i < 2; ++i) { L.U[i] = o; o += align256(n * es); }
+  // Fields beyond the 256 MB last-level cache start 33 x 256 bytes further apart:
+  // a step reads and writes the same cell of all four at a time, and where their
+  // starts are equal modulo a large power of two these accesses meet in the same
+  // memory banks (8192^2 FP32 at its default geometry with the frame 280-312 us a
+  // step, 255-258 apart; without it 274-301 and 250; pf_step_diffusion 273 and
+  // 265).  Within the cache it gains nothing (4096^2 with grains 104.8 and 106.0).
+  const size_t apart = 4 * n * es > ((size_t)256 << 20) ? 33 * 256 : 0;
+  for (int i = 0; i < 2; ++i) { L.psi[i] = o; o += align256(n * es) + apart; }
+  for (int i = 0; i < 2; ++i) { L.U[i] = o; o += align256(n * es) + apart; }
   L.grain = o; o += align256(p->n_grains > 1 ? n : 1);
   L.grain2 = o; o += align256(p->dynamic_grains ? n : 1);  // the next level's map
   L.rot = o; o += align256((size_t)(p->n_grains > 0 ? p->n_grains : 1) * 9 * es);
