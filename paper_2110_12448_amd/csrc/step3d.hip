@@ -55,7 +55,7 @@ struct Rot3 {
 template <typename T, int comp>
 __device__ __forceinline__ T aniso3(T gx, T gy, T gz, const Rot3<T> &R, const Coef<T> &c,
                                     T eps) {
-  // (below the guard r2 may be inf: the selects drop what it feeds)
+  // (below the guard r2 may be inf, in FP64 NaN: the selects drop what it feeds)
   T g2 = gx * gx + gy * gy + gz * gz;
   pause_issue(g2);
   T r2 = Math<T>::rcp(g2);
