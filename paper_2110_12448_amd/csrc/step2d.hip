@@ -822,12 +822,44 @@ Geom2D geom2d(int nx, int ny, int seg, int ncu, bool share) {
   return g;
 }
 
+// LDS a workgroup asks for beside its own 2 KB, so that 3 or 2 of them fit the
+// 160 KB of a CU: that many waves per SIMD.
+constexpr unsigned kLds3Waves = 50 * 1024, kLds2Waves = 60 * 1024;
+
+// Fewer waves in flight where the light FP32 single-grain variants run near the
+// HBM's rate on fields beyond its last-level cache: there more waves only spread
+// the accesses, worst where rows are whole 128-byte lines, so that a strip's
+// pieces of every row fall on the lines in the same way.  us a step at the
+// default geometry, unlimited / 3 / 2 waves per SIMD:
+//   approximated current on shells, moving frame
+//     6000^2, 12000x4000 (0.6, 0.8 GB)    140 / 149 / 183,  185 / 192 / 233
+//     8192^2, 16384x4096 (1.1 GB)         256 / 263 / 315,  300 / 272 / 319
+//     12000x11000, 11990x10000 (2 GB)     598 / 502 / 590,  449 / 457 / 541
+//   full current on two-point faces
+//     8192^2, 12000x11000, 11000x9000     255 / 262 / 314,  595 / 505 / 592,  373 / 383 / 454
+//   approximated current on two-point faces
+//     4096^2 (0.3 GB), 6000^2             58 / 61 / 71,     147 / 135 / 159
+//     11990x10000, 8192^2, 12000x11000    469 / 429 / 463,  290 / 252 / 268,  603 / 574 / 509
+// The FP64, multi-grain and full-current shell variants take more time a cell and
+// lose up to 20% with 3.
+template <typename T, int kAT>
+unsigned lds_for_waves(int nx, int ny, bool multi) {
+  if (sizeof(T) != 4 || multi) return 0;
+  const double bytes = 16.0 * nx * ny;  // psi and U, both buffers
+  const bool lines = bytes >= 1024.0 * 1048576.0 && nx % 32 == 0;
+  if (kAT == kAtApproxShells || kAT == kAtFullTwoPoint) return lines ? kLds3Waves : 0;
+  if (kAT == kAtApproxTwoPoint)
+    return lines ? kLds2Waves : bytes > 512.0 * 1048576.0 ? kLds3Waves : 0;
+  return 0;
+}
+
 template <typename T, int kAT>
 void launch_step2d_at(const Step2DArgs<T> &a, const Geom2D &g, bool frozen, bool reduce,
                       bool multi, hipStream_t st) {
   dim3 grid(g.blocks), block(256);
+  const unsigned lds = lds_for_waves<T, kAT>(a.nx, a.ny, multi);
 #define PF_L2(F, R, MU) \
-  hipLaunchKernelGGL((step2d_kernel<T, F, R, MU, kAT>), grid, block, 0, st, a)
+  hipLaunchKernelGGL((step2d_kernel<T, F, R, MU, kAT>), grid, block, lds, st, a)
   if (frozen) {
     if (reduce) { if (multi) PF_L2(true, true, true); else PF_L2(true, true, false); }
     else { if (multi) PF_L2(true, false, true); else PF_L2(true, false, false); }
